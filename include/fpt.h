@@ -380,8 +380,9 @@ int fpt_noise_table_bessel2d(const fpt_potential *pot, double sigma, int32_t n, 
  * the Bessel Wronskian, -2/pi, so B_k needs J_nu only and every nu > 0 works.  A node at or above phi_start, or
  * never reached (the trajectory is followed until phi < phi_lo, eps1 >= 1 or
  * N > 200), keeps fac = 1.  A node at phi_T takes the mode before the kink.
- * Computed by device kernels on the current device (a one-thread trajectory
- * kernel, then one thread per node; about 50 MB of device scratch for the call).
+ * Computed by device kernels on the current device (the trajectory by one wave in
+ * long strides, then a thread per segment of each node's mode; about 60 MB of device
+ * scratch for the call).
  * Errors: FPT_EINVAL (n out of 1..FPT_MAX_TABLE, sigma outside (0, 2], V <= 0 or
  * nu^2 <= 0 at a node, non-finite or eps1 >= 1 start, or a reached node whose
  * mode would start before N = 0 -- start the trajectory earlier), FPT_EHIP. */

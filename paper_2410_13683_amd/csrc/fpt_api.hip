@@ -238,7 +238,7 @@ extern "C" int fpt_noise_table_matched_time(const fpt_potential *pot, double sig
     if (!S_out || !tan_out) return fail(FPT_EINVAL, "output arrays are NULL");
     const double h = (n > 1) ? (t_hi - t_lo) / (double)(n - 1) : 0.0;
     const double N_after = (n > 1 ? t_hi : t_lo) + 2e-4;   // one sample beyond the last node
-    const size_t out_off = (fpt::matched_time_scratch_bytes() + 255) & ~(size_t)255;
+    const size_t out_off = (fpt::matched_scratch_bytes(n) + 255) & ~(size_t)255;
     char *d = nullptr;
     HIP_TRY(hipMalloc(&d, out_off + 4 * sizeof(double) * n + sizeof(int)));
     double *d_S = reinterpret_cast<double *>(d + out_off);
@@ -281,7 +281,7 @@ extern "C" int fpt_noise_table_bessel2d_time(const fpt_potential *pot, double si
     if (!Xpp_out || !Xpq_out || !Xqq_out) return fail(FPT_EINVAL, "output arrays are NULL");
     const double h = (n > 1) ? (t_hi - t_lo) / (double)(n - 1) : 0.0;
     const double N_after = (n > 1 ? t_hi : t_lo) + 2e-4;   // one sample beyond the last node
-    const size_t out_off = (fpt::matched_time_scratch_bytes() + 255) & ~(size_t)255;
+    const size_t out_off = (fpt::bessel2d_time_scratch_bytes() + 255) & ~(size_t)255;
     char *d = nullptr;
     HIP_TRY(hipMalloc(&d, out_off + 4 * sizeof(double) * n + sizeof(int)));
     double *d_X = reinterpret_cast<double *>(d + out_off);

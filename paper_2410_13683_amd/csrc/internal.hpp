@@ -186,7 +186,8 @@ hipError_t mlp_adam(float *params, float *m, float *v, const float *grad, int n,
                     double beta2, double eps, double bc1, double bc2, hipStream_t stream);
 
 // Bessel-matched noise table (fpt_table.hip).  Scratch: kMatchCap trajectory samples
-// (N, phi, pi) then n + 1 ints; matched_scratch_bytes(n) bytes.  d_status collects
+// (N, phi, pi), its strides, then per node the mode's job, its segments' propagators and its first
+// sample; matched_scratch_bytes(n) bytes (phi and time nodes alike).  d_status collects
 // 1 (V <= 0 or nu^2 <= 0 at a node), 2 (a node reached before its mode can start),
 // 4 (non-finite or zero B_k).
 constexpr int kMatchCap = (1 << 21) + 16;
@@ -195,13 +196,14 @@ hipError_t matched_table_launch(const PotParams &pot, double sigma, int n, doubl
                                 double phi_start, double pi_start, void *scratch, double *d_S, double *d_tan,
                                 double *d_fac, int *d_status, hipStream_t stream);
 // Time nodes N_ref + t_lo + j h after the trajectory passes phi_ref; the trajectory is followed
-// until N_ref + N_after.  Scratch: matched_time_scratch_bytes().  d_status as above plus 16 (no
-// passage of phi_ref, or a node outside the followed trajectory).
-size_t matched_time_scratch_bytes();
+// until N_ref + N_after at least.  d_status as above plus 16 (no passage of phi_ref, or a node
+// outside the followed trajectory).
 hipError_t matched_time_launch(const PotParams &pot, double sigma, int n, double t_lo, double h, double phi_start,
                                double pi_start, double phi_ref, double N_after, void *scratch, double *d_S,
                                double *d_tan, double *d_fac, double *d_phi, int *d_status, hipStream_t stream);
-// The 2D Bunch-Davies covariance on the same time nodes (scratch as above; d_status 1 or 16).
+// The 2D Bunch-Davies covariance on the same time nodes (scratch: the trajectory's part,
+// bessel2d_time_scratch_bytes(); d_status 1 or 16).
+size_t bessel2d_time_scratch_bytes();
 hipError_t bessel2d_time_launch(const PotParams &pot, double sigma, int n, double t_lo, double h, double phi_start,
                                 double pi_start, double phi_ref, double N_after, void *scratch, double *d_Xpp,
                                 double *d_Xpq, double *d_Xqq, double *d_phi, int *d_status, hipStream_t stream);
