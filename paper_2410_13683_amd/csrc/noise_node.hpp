@@ -5,8 +5,8 @@
 // -k eta = sigma: with y = -k eta, delta phi_k = H k^(-3/2) F(y), F = y^(3/2) (A J_nu + B Y_nu),
 // delta pi_k = H k^(-3/2) (-y F'(y)), so Xi = H^2/(2 pi^2) [[|F|^2, Re(F conj G)], [., |G|^2]]
 // with G = -y F'.  Y_nu = (J_nu cos nu pi - J_-nu)/sin nu pi turns F into alpha_+ y^(3/2) J_nu +
-// alpha_- y^(3/2) J_-nu, each J_mu summed as its power series (30 terms: below 1e-40 of the
-// leading term for sigma <= 2).  nu^2 = 9/4 - 3 (V''/V - (V'/V)^2) and H^2 = V/3 as for the 1D
+// alpha_- y^(3/2) J_-nu, each J_mu summed as its power series (at most 30 terms: below 1e-40 of the
+// leading term for sigma <= 2), each term from the one before.  nu^2 = 9/4 - 3 (V''/V - (V'/V)^2) and H^2 = V/3 as for the 1D
 // table.
 #pragma once
 
@@ -49,15 +49,21 @@ __device__ inline bool bessel2d_node(const PotParams &pp, double sigma, double p
     const Cplx alpha[2] = {cadd(Ak, cscale(Bk, cs / sn)), cscale(Bk, -1.0 / sn)};
     const double mus[2] = {nu, -nu};
     Cplx F = {0.0, 0.0}, G = {0.0, 0.0};
+    // term_m = (-1)^m sigma^p / (m! Gamma(m + mu + 1) 2^(2m + mu)), p = 2m + mu + 3/2.  With powers and
+    // gamma functions taken anew for every term, a node cost 240 library calls and 2048 nodes 103 us on
+    // their 32 waves; the ratio of neighbouring terms leaves two of each.
     for (int k = 0; k < 2; ++k) {
-        const double mu = mus[k];
-        for (int m = 0; m < 30; ++m) {
-            const double p = 2.0 * m + mu + 1.5;
-            const double term = ((m & 1) ? -1.0 : 1.0) * pow(sigma, p) /
-                                (tgamma((double)m + 1.0) * tgamma((double)m + mu + 1.0) * pow(2.0, 2.0 * m + mu));
-            F = cadd(F, cscale(alpha[k], term));
-            G = cadd(G, cscale(alpha[k], -p * term));
+        const double mu = mus[k], q = -0.25 * sigma * sigma;
+        double term = sigma * sqrt(sigma) * pow(0.5 * sigma, mu) / tgamma(mu + 1.0);
+        double f = term, g = (mu + 1.5) * term;
+        for (int m = 1; m < 30; ++m) {
+            term *= q / ((double)m * ((double)m + mu));
+            f += term;
+            g += (2.0 * m + mu + 1.5) * term;
+            if (fabs(term) * 1e3 < 1e-18 * fmin(fabs(f), fabs(g)) && (double)m > nu) break;
         }
+        F = cadd(F, cscale(alpha[k], f));
+        G = cadd(G, cscale(alpha[k], -g));
     }
     const double c = (V / 3.0) / (2.0 * M_PI * M_PI);
     Xpp = c * (F.re * F.re + F.im * F.im);
