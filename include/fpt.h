@@ -195,7 +195,8 @@ typedef struct {
  * block_size (64..1024, multiple of 64), blocks_per_cu (>= 1) and chunk
  * (steps between retire/refill, multiple of 4; FP32 state steps in groups of
  * 16, 4 with mlp_every > 0, and rounds it up to a multiple of the group) select
- * the launch; 0 picks the built-in default.  They never change results. */
+ * the launch; 0 picks the built-in default (with block_size and blocks_per_cu both
+ * 0, blocks that fit the run's trajectory count).  They never change results. */
 typedef struct {
     int32_t precision;
     int32_t bins_kind, n_bins;

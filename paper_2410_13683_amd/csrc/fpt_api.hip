@@ -737,6 +737,28 @@ static int occupancy_grid(const void *fn, int block, size_t lds, int cu_count, i
     return FPT_OK;
 }
 
+// The launch shape of a run of n_traj trajectories: the caller's block size and blocks per CU where
+// given, else 1024 threads and as many blocks as fit.  A run of less than a trajectory per lane of that
+// grid is spread instead: one block per CU of just the waves it needs (a block's waves sit on the CU's
+// SIMDs in turn), since up to a trajectory per lane the time is that of one trajectory beside its
+// SIMD's other waves.  On full blocks the first ones to reach the cursor filled all their 16 waves
+// while other CUs stood idle: 1e5 FP32 trajectories (slow roll -> ultra-slow roll) took 12 to 18 ms from
+// launch to launch and take 11.9; 65,536 FP64 ones 44.1 -> 24.3 ms, 131,072 56.6 -> 32.8 ms; 1e4 of the
+// linear problem 1.57 -> 1.42 ms.  From one wave on every slot of the full grid (262,144 trajectories)
+// the shapes are the same.
+static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_traj, int &grid, int &block)
+{
+    block = c->opt.block_size ? c->opt.block_size : 1024;
+    const int rc = occupancy_grid(fn, block, lds, c->cu_count, c->opt.blocks_per_cu, grid);
+    if (rc || c->opt.block_size || c->opt.blocks_per_cu) return rc;
+    const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
+    if (waves >= (uint64_t)grid * (uint64_t)(block / 64)) return FPT_OK;
+    const uint64_t per_cu = std::min<uint64_t>((waves + cus - 1) / cus, (uint64_t)(block / 64));
+    block = 64 * (int)per_cu;
+    grid = (int)std::min<uint64_t>((uint64_t)grid, (waves + per_cu - 1) / per_cu);
+    return FPT_OK;
+}
+
 extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset,
                        void *hip_stream, double *d_N, double *d_lnw, uint32_t *d_steps)
 {
@@ -761,8 +783,7 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     p.d_lnw = d_lnw;
     p.d_steps = d_steps;
     p.cursor = c->cursor;
-    const int block = c->opt.block_size ? c->opt.block_size : 1024;
-    int grid = 0;
+    int grid = 0, block = 0;
     const bool two_d = c->inst.noise_dim == 2;
     // the learned control runs its tabulated network, or the network itself every mlp_every steps
     const bool exact = c->inst.bias_kind == kBiasMlp && c->inst.mlp_every > 0;
@@ -774,7 +795,7 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     const size_t lds = two_d ? em2d_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision)
                              : em_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision, grid_cells(c->inst),
                                             exact);
-    int rc = occupancy_grid(fn, block, lds, c->cu_count, c->opt.blocks_per_cu, grid);
+    const int rc = run_shape(c, fn, lds, n_traj, grid, block);
     if (rc) return rc;
     HIP_TRY(zero_words(p.cursor, 1, s));
     HIP_TRY(hipEventRecord(c->ev_start, s));
@@ -970,12 +991,10 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
     p.d_lnw = d_lnw;
     p.d_steps = d_steps;
     const int block = c->opt.block_size ? c->opt.block_size : 1024;
-    int grid_em = 0, grid_rp = 0;
+    int grid_rp = 0;
     const int n_cells = grid_cells(c->inst);
-    rc = occupancy_grid(em_kernel_ptr(c->precision, kBiasMlp, tab_mode(c->inst), c->inst.all_S_pos != 0), block,
-                        em_lds_bytes(c->opt.n_bins, c->inst.n_tab, c->precision, n_cells), c->cu_count,
-                        c->opt.blocks_per_cu, grid_em);
-    if (rc) return rc;
+    const void *em_fn = em_kernel_ptr(c->precision, kBiasMlp, tab_mode(c->inst), c->inst.all_S_pos != 0);
+    const size_t em_lds = em_lds_bytes(c->opt.n_bins, c->inst.n_tab, c->precision, n_cells);
     rc = occupancy_grid(replay_kernel_ptr(c->precision, c->inst.all_S_pos != 0), block,
                         replay_lds_bytes(c->inst.n_tab, c->precision, n_cells, (int)n_nodes), c->cu_count,
                         c->opt.blocks_per_cu, grid_rp);
@@ -996,7 +1015,10 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
         HIP_TRY(zero_words(&cnt[3], 1, s));
         p.traj_offset = traj_offset + done;
         p.n_traj = m;
-        HIP_TRY(em_launch(p, c->precision, grid_em, block, s));
+        int grid_em = 0, block_em = 0;
+        rc = run_shape(c, em_fn, em_lds, m, grid_em, block_em);
+        if (rc) return rc;
+        HIP_TRY(em_launch(p, c->precision, grid_em, block_em, s));
         HIP_TRY(mlp_tail_compact(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, d_tail, &cnt[0],
                                  &cnt[1], c->d_J, s));
         HIP_TRY(replay_launch(rp, c->precision, grid_rp, block, s));

@@ -1712,7 +1712,12 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY replay_kernel(ReplayPar
     RetireTo rt{};
     const ReplayTo rp{p.tail, l_G, p.mismatch};
     const uint64_t n_tail = *p.n_tail;
-    if (PREC == 0)
+    // The list's length is known on the device alone, so the grid is a full one; where the list does not
+    // fill it, each block's first ceil(waves/blocks) waves share it (as run_shape does for fpt_run).
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x) / 64;
+    if (wave >= ((n_tail + 63) / 64 + gridDim.x - 1) / gridDim.x) {
+        // nothing to replay here
+    } else if (PREC == 0)
         lanes_fp64<kBiasMlp, true, ALLPOS, true>(I, p.run, reinterpret_cast<const double2 *>(l_tab),
                                                  reinterpret_cast<const double2 *>(l_grid), rt, rp, p.cursor, n_tail,
                                                  0);
