@@ -746,9 +746,10 @@ static int occupancy_grid(const void *fn, int block, size_t lds, int cu_count, i
 // launch to launch and take 11.9; 65,536 FP64 ones 44.1 -> 24.3 ms, 131,072 56.6 -> 32.8 ms; 1e4 of the
 // linear problem 1.57 -> 1.42 ms.  From one wave on every slot of the full grid (262,144 trajectories)
 // the shapes are the same.
-static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_traj, int &grid, int &block)
+static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_traj, int &grid, int &block,
+                     int block_max = 1024)
 {
-    block = c->opt.block_size ? c->opt.block_size : 1024;
+    block = std::min(c->opt.block_size ? c->opt.block_size : 1024, block_max);
     const int rc = occupancy_grid(fn, block, lds, c->cu_count, c->opt.blocks_per_cu, grid);
     if (rc || c->opt.block_size || c->opt.blocks_per_cu) return rc;
     const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
@@ -795,7 +796,7 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     const size_t lds = two_d ? em2d_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision)
                              : em_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision, grid_cells(c->inst),
                                             exact);
-    const int rc = run_shape(c, fn, lds, n_traj, grid, block);
+    const int rc = run_shape(c, fn, lds, n_traj, grid, block, exact && c->precision == FPT_FP32_STATE ? kMaxBlockNet32 : 1024);
     if (rc) return rc;
     HIP_TRY(zero_words(p.cursor, 1, s));
     HIP_TRY(hipEventRecord(c->ev_start, s));

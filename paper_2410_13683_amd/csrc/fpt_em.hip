@@ -552,11 +552,20 @@ __device__ __forceinline__ void grad_add(T s[4], T c, T f0, T f1)
 // at a time, each pass recomputing the 64 first-layer activations, so that a lane holds eight
 // accumulators instead of 64 activations.
 //
-// FP32 state: the parameters are read in place from global memory through the constant address
-// space.  Every lane of a wave reads the same word, so the loads become scalar loads and the
-// multiply-adds take the weights as scalar operands (no LDS traffic); a lane keeps its 64
-// first-layer activations in registers.  tanh s = 1 - 2/(e^(2s) + 1) from the hardware exp2 and
-// reciprocal, exactly +-1 for large |s|.
+// FP32 state: the second layer, 64 x 64 for the wave's 64 states, runs on the matrix cores as 128
+// v_mfma_f32_32x32x1 (two blocks of 32 states, one input unit per instruction).  Such an instruction is
+// one fused multiply-add per element, rounded like v_fma_f32 (bit for bit over 8e5 elements of mixed
+// scales), so the sums are those of a chain of multiply-adds in the order of the input units, two
+// chains per output unit (even and odd units).  A lane holds its state's input unit as the B operand
+// and output unit lane % 32 of the weights as A, staged in LDS so that one 16-byte read serves four
+// instructions; W1, b1 and W3 are read in place through the constant address space (scalar loads).
+// Bound: the 128 instructions take 9.6e3 cycles an evaluation (75 each measured) and the FP32 vector
+// work, which does not run beside FP32 matrix instructions, some 5e3 more (256 exp2 and reciprocals at
+// 8 cycles among it); 1.6e4 measured.  The 128 accumulators leave two waves per SIMD.  Before, the 4096
+// multiply-adds took the weights as scalar operands, 17.9 KB through the 16 KB scalar cache, whose
+// waits left 2e4 to 5.6e4 cycles an evaluation: 1e5 trajectories at k = 16 went from 238 to 104 ms,
+// 1000 trajectories (one wave per SIMD) from 147 to 67 ms.
+// tanh s = 1 - 2/(e^(2s) + 1) from the hardware exp2 and reciprocal, exactly +-1 for large |s|.
 // ---------------------------------------------------------------------------
 constexpr int kMlpChunk = 8;
 constexpr int kMlpLdsWords = kMlpHidden * kMlpHidden + 2 * kMlpHidden + 3 * kMlpHidden + 1;
@@ -602,6 +611,20 @@ __device__ __forceinline__ double mlp_out0_64(const double *l_w, double x0, doub
 }
 
 typedef __attribute__((address_space(4))) const float const_float;
+typedef float float32x __attribute__((ext_vector_type(32)));
+
+// The LDS copy of W2 and b2 for the matrix instructions: for input units 2j and 2j + 1 and r = 0..31
+// the four weights (W2[r][2j], W2[r + 32][2j], W2[r][2j + 1], W2[r + 32][2j + 1]), then b2.
+constexpr size_t kMlpLdsBytes32 = (size_t)(kMlpHidden * kMlpHidden + kMlpHidden) * sizeof(float);
+
+__device__ __forceinline__ void stage_mlp32(const float *params, float *l_w)
+{
+    constexpr int H = kMlpHidden;
+    for (int k = threadIdx.x; k < H * H + H; k += blockDim.x) {
+        const int j = 2 * (k / 128) + (k >> 1 & 1), o = (k / 4) % 32 + 32 * (k & 1);
+        l_w[k] = params[k < H * H ? kOffW2 + o * H + j : kOffB2 + (k - H * H)];
+    }
+}
 
 // z[j] by a run-time index, as selects (folded away where j is a constant)
 template <typename T>
@@ -616,25 +639,57 @@ __device__ __forceinline__ float mlp_tanh32(float s)
     return fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
 }
 
-__device__ __forceinline__ float mlp_out0_32(const_float *p, float x0, float x1)
+// Every lane of the wave must take part (the weights of output unit lane % 32 come from each lane).
+__device__ __forceinline__ float mlp_out0_32(const_float *p, const float *l_w, float x0, float x1)
 {
     constexpr int H = kMlpHidden;
-    float h[H];
+    const int lane = (int)__lane_id();
+    // accumulators [units 0..31, units 32..63]: element 16 b + 4 g + q of a lane is output unit
+    // 8 g + 4 (lane / 32) + q of state 32 b + lane % 32
+    float32x e[2], o[2];
+    const float4 *l_b = reinterpret_cast<const float4 *>(l_w + H * H) + (lane >> 5);
 #pragma unroll
-    for (int j = 0; j < H; ++j)
-        h[j] = mlp_tanh32(fmaf(p[kOffW1 + 2 * j], x0, fmaf(p[kOffW1 + 2 * j + 1], x1, p[kOffB1 + j])));
-    float out = p[kOffB3];
-    for (int o = 0; o < H; ++o) {
-        const_float *row = p + kOffW2 + o * H;
-        // two partial sums: two independent chains of multiply-adds
-        float s0 = p[kOffB2 + o], s1 = 0.0f;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int j = 0; j < H; j += 2) {
-            s0 = fmaf(row[j], h[j], s0);
-            s1 = fmaf(row[j + 1], h[j + 1], s1);
+        for (int g = 0; g < 4; ++g) {
+            const float4 b = l_b[8 * h + 2 * g];
+            const float v[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                e[h][4 * g + q] = e[h][16 + 4 * g + q] = v[q];
+                o[h][4 * g + q] = o[h][16 + 4 * g + q] = 0.0f;
+            }
         }
-        out = fmaf(p[kOffW3 + o], mlp_tanh32(s0 + s1), out);
+    const float4 *l_a = reinterpret_cast<const float4 *>(l_w) + (lane & 31);
+#pragma unroll 4
+    for (int j = 0; j < H; j += 2) {
+        const float4 w = l_a[16 * j];
+        const float h0 = mlp_tanh32(fmaf(p[kOffW1 + 2 * j], x0, fmaf(p[kOffW1 + 2 * j + 1], x1, p[kOffB1 + j])));
+        const float h1 = mlp_tanh32(fmaf(p[kOffW1 + 2 * j + 2], x0, fmaf(p[kOffW1 + 2 * j + 3], x1, p[kOffB1 + j + 1])));
+        e[0] = __builtin_amdgcn_mfma_f32_32x32x1f32(w.x, h0, e[0], 0, 0, 0);
+        e[1] = __builtin_amdgcn_mfma_f32_32x32x1f32(w.y, h0, e[1], 0, 0, 0);
+        o[0] = __builtin_amdgcn_mfma_f32_32x32x1f32(w.z, h1, o[0], 0, 0, 0);
+        o[1] = __builtin_amdgcn_mfma_f32_32x32x1f32(w.w, h1, o[1], 0, 0, 0);
     }
+    float out = p[kOffB3];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            // the halves of the wave trade: then every lane has units 8 g + q (u) and 8 g + 4 + q (v) of its own state
+            float u[4], v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float s0 = e[h][4 * g + q] + o[h][4 * g + q], s1 = e[h][16 + 4 * g + q] + o[h][16 + 4 * g + q];
+                const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
+                u[q] = __uint_as_float(t[0]);
+                v[q] = __uint_as_float(t[1]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out = fmaf(p[kOffW3 + 32 * h + 8 * g + q], mlp_tanh32(u[q]), out);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out = fmaf(p[kOffW3 + 32 * h + 8 * g + 4 + q], mlp_tanh32(v[q]), out);
+        }
     return out;
 }
 
@@ -1080,10 +1135,12 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             float f0 = 0.0f, f1 = 0.0f;
             if (BIAS == kBiasMlp) a = grid_amp32(gc, l_grid, xs, ps, cell, f0, f1);
             if (BIAS == kBiasMlpExact) {
-                if (n + j == next_eval) {
-                    a_held = mlp_out0_32(wp, fmaf(xs, nq.k0, nq.off0),
-                                         fmaf(__builtin_amdgcn_logf(fmaxf(fabsf(ps), 1e-30f)), nq.k1, nq.off1));
-                    next_eval += every;
+                const bool due = n + j == next_eval;
+                if (__any(due)) {      // by the whole wave; lanes at other phases keep what they hold
+                    const float v = mlp_out0_32(wp, reinterpret_cast<const float *>(l_grid), fmaf(xs, nq.k0, nq.off0),
+                                                fmaf(__builtin_amdgcn_logf(fmaxf(fabsf(ps), 1e-30f)), nq.k1, nq.off1));
+                    a_held = due ? v : a_held;
+                    next_eval += due ? every : 0u;
                 }
                 a = a_held;
             }
@@ -1643,7 +1700,8 @@ __device__ __forceinline__ RetireTo retire_to(const EmParams &p, const LdsAcc &a
 }
 
 template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
-__global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em_kernel(EmParams p)
+__global__ void __launch_bounds__(BIAS == kBiasMlpExact && PREC == 1 ? kMaxBlockNet32 : 1024) FPT_EM_OCCUPANCY
+em_kernel(EmParams p)
 {
     static_assert(POT == kPotPiecewiseLinear || (PREC == 0 && (BIAS == kBiasNone || BIAS == kBiasConst)),
                   "the bump runs in FP64 only, without a learned bias");
@@ -1656,6 +1714,7 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em_kernel(EmParams p)
     else stage_table32(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
     if (BIAS == kBiasMlp) stage_grid<PREC>(p.inst, l_grid);
     if (BIAS == kBiasMlpExact && PREC == 0) stage_mlp64(p.inst.mlp_params, reinterpret_cast<double *>(l_grid));
+    if (BIAS == kBiasMlpExact && PREC == 1) stage_mlp32(p.inst.mlp_params, reinterpret_cast<float *>(l_grid));
     __syncthreads();
     const RetireTo rt = retire_to(p, acc);
     const ReplayTo rp{nullptr, nullptr, nullptr};
@@ -1833,8 +1892,8 @@ struct KTab {
 
 size_t em_lds_bytes(int n_bins, int n_tab, int precision, int n_cells, bool mlp_exact)
 {
-    // the exact network stages its parameters (FP64 state) instead of the tabulated cells
-    const size_t bias = mlp_exact ? (precision == 0 ? kMlpLdsBytes64 : 0) : cell_bytes(precision, n_cells);
+    // the exact network stages its parameters instead of the tabulated cells
+    const size_t bias = mlp_exact ? (precision == 0 ? kMlpLdsBytes64 : kMlpLdsBytes32) : cell_bytes(precision, n_cells);
     return align16(acc_bytes(n_bins)) + tab_bytes(precision, n_tab) + bias;
 }
 

@@ -15,6 +15,7 @@ enum : int { kBiasNone = 0, kBiasConst = 1, kBiasMlp = 2 };
 // kernel-side bias variant (not in the ABI): the learned control's network evaluated exactly every
 // mlp_every steps instead of read from its table
 constexpr int kBiasMlpExact = 3;
+constexpr int kMaxBlockNet32 = 512;   // largest block of its FP32 kernel (two waves per SIMD)
 enum : int { kBinsLinear = 0, kBinsLog = 1 };
 
 constexpr uint32_t kFlagCensored = 0x80000000u;
