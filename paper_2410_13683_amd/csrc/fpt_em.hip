@@ -710,6 +710,34 @@ __device__ __forceinline__ NetConsts32 net_consts32(const Inst &I)
 }
 
 // ---------------------------------------------------------------------------
+// Paired waves.  A run that leaves SIMDs short of waves is bound by the latency of one wave's step:
+// half of it forms the random numbers, which do not depend on the state.  There each integrating wave
+// gets a partner that forms its normals, one trajectory per lane and no refill: the partner fills the
+// wave's LDS buffer with the normals of the next kFeedSteps steps while the wave takes the current
+// ones, from registers.  Both waves of every pair run the same loop,
+//   fill / step | barrier | (take the buffer, say whether the wave has a live lane) | barrier | all done?
+// and leave it together, at the first turn in which no integrating wave of the block has a live lane.
+// That answer is in the flags of the turn's parity, which are next written two barriers later, so every
+// wave of the block reads the same one.  The arithmetic is that of the unpaired kernel.
+// ---------------------------------------------------------------------------
+struct Feed {
+    unsigned char *buf;      // this pair's buffer (LDS)
+    uint32_t *flags;         // [2][kFeedMaxPairs] (LDS): the pair's wave has a live lane
+    int pair, n_pairs;       // this pair and the block's pairs
+    uint64_t first;          // relative index of lane 0's trajectory
+};
+
+// One turn's end: flags up, barrier, and whether any pair goes on.
+__device__ __forceinline__ bool feed_goes_on(const Feed &f, uint32_t turn)
+{
+    __syncthreads();
+    uint32_t any = 0;
+    const uint32_t *fl = f.flags + (turn & 1) * kFeedMaxPairs;
+    for (int i = 0; i < f.n_pairs; ++i) any |= fl[i];
+    return __builtin_amdgcn_readfirstlane(any) != 0;
+}
+
+// ---------------------------------------------------------------------------
 // FP64 state: the lanes of one wave integrate trajectories of instance I,
 // claimed from `cursor` (global or LDS), until the range is exhausted.
 //
@@ -727,10 +755,10 @@ __device__ __forceinline__ NetConsts32 net_consts32(const Inst &I)
 // ---------------------------------------------------------------------------
 // TAB: 0 a single node (constant noise); 1 nodes in phi; 2 nodes in the run's time n dN (the
 // table's phi_lo and inv_h then refer to N).
-template <int BIAS, int TAB, bool ALLPOS, bool GRAD, int POT = kPotPiecewiseLinear>
+template <int BIAS, int TAB, bool ALLPOS, bool GRAD, int POT = kPotPiecewiseLinear, bool FEED = false>
 __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, const double2 *l_tab, const double2 *l_grid,
                                            const RetireTo &rt, const ReplayTo &rp, unsigned long long *cursor,
-                                           uint64_t n_traj, uint64_t traj_offset)
+                                           uint64_t n_traj, uint64_t traj_offset, const Feed &feed = Feed{})
 {
     static_assert(!GRAD || BIAS == kBiasMlp, "replay needs the tabulated control");
     constexpr bool LEARNED = BIAS == kBiasMlp || BIAS == kBiasMlpExact;
@@ -751,8 +779,8 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     const double s_plus = in_vgpr(dk.s_plus), s_minus = in_vgpr(dk.s_minus);
 
     bool exhausted = false;
-    uint64_t rel = 0;
-    bool has = claim(true, rel, cursor, n_traj, exhausted);
+    uint64_t rel = FEED ? feed.first + __lane_id() : 0;
+    bool has = FEED ? rel < n_traj : claim(true, rel, cursor, n_traj, exhausted);
     bool live = has;          // has a trajectory that has not ended yet
     double phi = I.phi_in, pi_ = I.pi_in, lnw = 0.0;
     uint32_t n = 0;
@@ -766,7 +794,8 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
         traj = rp.tail[rel].traj;
         ww = rp.tail[rel].ww;
     }
-    PhiloxPre pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+    PhiloxPre pre{};
+    if (!FEED) pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
 
     auto group = [&](auto censor_tag, const double z[4]) {
         constexpr bool CENSOR = decltype(censor_tag)::value;
@@ -867,6 +896,27 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
         }
     };
 
+    if constexpr (FEED) {
+        const double2 *buf = reinterpret_cast<const double2 *>(feed.buf) + __lane_id();
+        for (uint32_t turn = 0;; ++turn) {
+            __syncthreads();
+            double2 v[kFeedSteps / 2];
+#pragma unroll
+            for (int q = 0; q < kFeedSteps / 2; ++q) v[q] = buf[64 * q];
+            feed.flags[(turn & 1) * kFeedMaxPairs + feed.pair] = __any(live) ? 1u : 0u;
+            if (!feed_goes_on(feed, turn)) break;
+            if (!__any(live)) continue;
+#pragma unroll
+            for (int q = 0; q < kFeedSteps / 2; q += 2) {
+                const double z[4] = {v[q].x, v[q].y, v[q + 1].x, v[q + 1].y};
+                // all lanes are at the same step
+                if ((uint32_t)__builtin_amdgcn_readfirstlane(n) + 4 > I.max_steps)
+                    group(std::integral_constant<bool, true>(), z);
+                else group(std::integral_constant<bool, false>(), z);
+            }
+        }
+        return;
+    }
     while (__any(has)) {
         const uint32_t left = wave_steps_left(has, n, I.max_steps);
         for (int k = 0; k < R.chunk; k += 4) {
@@ -895,6 +945,29 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             }
             pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
         }
+    }
+}
+
+// The partner of a paired FP64 wave: the normals of kFeedSteps steps (two or more generator calls) a turn.
+__device__ __forceinline__ void feed_fp64(const Inst &I, const RunArgs &R, const double2 *l_bm, uint64_t traj_offset,
+                                          const Feed &feed)
+{
+    const PhiloxPre pre = philox_pre(traj_offset + feed.first + __lane_id(), I.instance, R.key0, R.key1);
+    double2 *buf = reinterpret_cast<double2 *>(feed.buf) + __lane_id();
+    uint32_t m = 0;
+    for (uint32_t turn = 0;; ++turn) {
+#pragma unroll
+        for (int q = 0; q < kFeedSteps / 2; q += 2) {
+            uint32_t w[4];
+            philox_call(m++, pre, R.key0, R.key1, w);
+            double2 a, b;
+            box_muller64(w[0], w[1], R.sqrt_dN, l_bm, a.x, a.y);
+            box_muller64(w[2], w[3], R.sqrt_dN, l_bm, b.x, b.y);
+            buf[64 * q] = a;
+            buf[64 * (q + 1)] = b;
+        }
+        __syncthreads();
+        if (!feed_goes_on(feed, turn)) break;
     }
 }
 
@@ -961,10 +1034,10 @@ __device__ __forceinline__ void box_muller32(uint32_t wa, uint32_t wb, float m2l
     zb = fmaf(rho, __builtin_amdgcn_sinf(ub), off);
 }
 
-template <int BIAS, int TAB, bool ALLPOS, bool GRAD>
+template <int BIAS, int TAB, bool ALLPOS, bool GRAD, bool FEED = false>
 __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, const float4 *l_tab, const float4 *l_grid,
                                            const RetireTo &rt, const ReplayTo &rp, unsigned long long *cursor,
-                                           uint64_t n_traj, uint64_t traj_offset)
+                                           uint64_t n_traj, uint64_t traj_offset, const Feed &feed = Feed{})
 {
     static_assert(!GRAD || BIAS == kBiasMlp, "replay needs the tabulated control");
     constexpr bool LEARNED = BIAS == kBiasMlp || BIAS == kBiasMlpExact;
@@ -988,8 +1061,8 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
     const float s_plus = in_vgpr(c.s_plus), s_minus = in_vgpr(c.s_minus);
 
     bool exhausted = false;
-    uint64_t rel = 0;
-    bool has = claim(true, rel, cursor, n_traj, exhausted);
+    uint64_t rel = FEED ? feed.first + __lane_id() : 0;
+    bool has = FEED ? rel < n_traj : claim(true, rel, cursor, n_traj, exhausted);
     bool live = has;          // has a trajectory that has not ended yet
     // state: x = xh + xl, pi = ph + pl; xs, ps their rounded sums (what a step reads; xs is formed
     // each step only where a step reads it, and otherwise once per group)
@@ -1009,7 +1082,8 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         traj = rp.tail[rel].traj;
         ww = rp.tail[rel].ww;
     }
-    PhiloxPre pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+    PhiloxPre pre{};
+    if (!FEED) pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
 
     // constant bias: each step's normal carries the drift shift, z = xi sqrt(dN) + c.adN with
     // c.adN = fl32(A dN), so the exponent of eq. (weight_A) in 1D over k steps,
@@ -1223,6 +1297,64 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         ph = ps;
     };
 
+    // One group from its normals; `may_cap`: a lane may reach max_steps in it.
+    auto run_group = [&](bool may_cap, const float z[G]) {
+        using T = std::integral_constant<bool, true>;
+        using F = std::integral_constant<bool, false>;
+        if constexpr (TAB == 1) {
+            // the record of the lane's interval at the group start
+            const float u0 = __builtin_amdgcn_fmed3f(fmaf(xs, c.inv_h, c.u_off), 0.0f, c.jtop);
+            const int j0 = (int)u0;
+            const float4 g_node = l_tab[j0];
+            const float2 g_rn = l_rtab[j0];
+            const float fh = fmaf(xh, c.inv_h, c.u_off - (float)j0);   // the fraction at x = xh
+            g_S = fmaf(fh, g_node.y, g_node.x);
+            g_dS = g_node.y * c.inv_h;
+            g_t = fmaf(fh, g_node.w, g_node.z);
+            g_dt = g_node.w * c.inv_h;
+            g_r = fmaf(fh, g_rn.y, g_rn.x);
+            g_dr = g_rn.y * c.inv_h;
+        }
+        if (may_cap) {
+            group(T(), F(), T(), z);
+        } else {
+            if constexpr (TAB == 1) {
+                if (__builtin_amdgcn_ballot_w64(live && g_r != g_r) != 0) {
+                    group(F(), F(), T(), z);
+                } else if constexpr (LEARNED) {
+                    group(F(), T(), T(), z);
+                } else {
+                    if (__builtin_amdgcn_ballot_w64(live && fabsf(ps) > pi_safe) == 0)
+                        group(F(), T(), F(), z);
+                    else group(F(), T(), T(), z);
+                }
+            } else {
+                group(F(), F(), T(), z);
+            }
+        }
+    };
+
+    if constexpr (FEED) {
+        static_assert(G == kFeedSteps32, "a turn is one group");
+        const float4 *buf = reinterpret_cast<const float4 *>(feed.buf) + __lane_id();
+        for (uint32_t turn = 0;; ++turn) {
+            __syncthreads();
+            float z[G];
+#pragma unroll
+            for (int q = 0; q < G / 4; ++q) {
+                const float4 v = buf[64 * q];
+                z[4 * q] = v.x;
+                z[4 * q + 1] = v.y;
+                z[4 * q + 2] = v.z;
+                z[4 * q + 3] = v.w;
+            }
+            feed.flags[(turn & 1) * kFeedMaxPairs + feed.pair] = __any(live) ? 1u : 0u;
+            if (!feed_goes_on(feed, turn)) break;
+            // all lanes are at the same step
+            if (__any(live)) run_group((uint32_t)__builtin_amdgcn_readfirstlane(n) + G > I.max_steps, z);
+        }
+        return;
+    }
     // n_hi: a wave-uniform upper bound on n over the lanes that hold a trajectory.  All lanes step
     // together and a refilled lane restarts at 0, so adding each chunk's steps keeps it a bound;
     // the exact maximum (a cross-lane reduction) is formed only once the bound comes within a
@@ -1243,39 +1375,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             const float off = (BIAS == kBiasConst) ? c.adN : 0.0f;
 #pragma unroll
             for (int q = 0; q < G; q += 2) box_muller32(w[q], w[q + 1], c.m2ln2_dN, off, z[q], z[q + 1]);
-            using T = std::integral_constant<bool, true>;
-            using F = std::integral_constant<bool, false>;
-            if constexpr (TAB == 1) {
-                // the record of the lane's interval at the group start
-                const float u0 = __builtin_amdgcn_fmed3f(fmaf(xs, c.inv_h, c.u_off), 0.0f, c.jtop);
-                const int j0 = (int)u0;
-                const float4 g_node = l_tab[j0];
-                const float2 g_rn = l_rtab[j0];
-                const float fh = fmaf(xh, c.inv_h, c.u_off - (float)j0);   // the fraction at x = xh
-                g_S = fmaf(fh, g_node.y, g_node.x);
-                g_dS = g_node.y * c.inv_h;
-                g_t = fmaf(fh, g_node.w, g_node.z);
-                g_dt = g_node.w * c.inv_h;
-                g_r = fmaf(fh, g_rn.y, g_rn.x);
-                g_dr = g_rn.y * c.inv_h;
-            }
-            if ((uint32_t)k + G > left) {
-                group(T(), F(), T(), z);
-            } else {
-                if constexpr (TAB == 1) {
-                    if (__builtin_amdgcn_ballot_w64(live && g_r != g_r) != 0) {
-                        group(F(), F(), T(), z);
-                    } else if constexpr (LEARNED) {
-                        group(F(), T(), T(), z);
-                    } else {
-                        if (__builtin_amdgcn_ballot_w64(live && fabsf(ps) > pi_safe) == 0)
-                            group(F(), T(), F(), z);
-                        else group(F(), T(), T(), z);
-                    }
-                } else {
-                    group(F(), F(), T(), z);
-                }
-            }
+            run_group((uint32_t)k + G > left, z);
         }
         n_hi += (uint32_t)k;
         if (!live) has = false;
@@ -1300,6 +1400,28 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         }
     }
 }
+// The partner of a paired FP32 wave: the shifted normals of one group (four generator calls) a turn.
+__device__ __forceinline__ void feed_fp32(const Inst &I, const RunArgs &R, uint64_t traj_offset, const Feed &feed)
+{
+    const F32Consts c = f32_consts(I, R);
+    const PhiloxPre pre = philox_pre(traj_offset + feed.first + __lane_id(), I.instance, R.key0, R.key1);
+    float4 *buf = reinterpret_cast<float4 *>(feed.buf) + __lane_id();
+    uint32_t m = 0;
+    for (uint32_t turn = 0;; ++turn) {
+#pragma unroll
+        for (int q = 0; q < kFeedSteps32 / 4; ++q) {
+            uint32_t w[4];
+            philox_call(m++, pre, R.key0, R.key1, w);
+            float4 v;
+            box_muller32(w[0], w[1], c.m2ln2_dN, c.adN, v.x, v.y);
+            box_muller32(w[2], w[3], c.m2ln2_dN, c.adN, v.z, v.w);
+            buf[64 * q] = v;
+        }
+        __syncthreads();
+        if (!feed_goes_on(feed, turn)) break;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // FP64 state with 2D noise (eq. full_langevin_equation): two normals per step,
 // noise S (xi_1, xi_2) sqrt(dN) with S the interpolated symmetric square root of
@@ -1730,6 +1852,43 @@ em_kernel(EmParams p)
     flush_lds_acc(acc, p.inst.acc);
 }
 
+// Paired waves: one trajectory per lane of the block's first half of waves, the second half forming
+// their normals (see Feed).  The grid covers the trajectories; p.cursor is not used.
+template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
+__global__ void __launch_bounds__(64 * 2 * kFeedMaxPairs) em_pair_kernel(EmParams p)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t flags[2 * kFeedMaxPairs];
+    const LdsAcc acc = lds_acc(smem, p.inst.hist.n_bins);
+    unsigned char *l_tab = smem + align16(acc_bytes(p.inst.hist.n_bins));
+    unsigned char *l_feed = l_tab + tab_bytes(PREC, p.inst.n_tab);
+    zero_lds_acc(acc);
+    if (PREC == 0) stage_table64(p.inst, reinterpret_cast<double2 *>(l_tab));
+    else stage_table32(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
+    __syncthreads();
+    const RetireTo rt = retire_to(p, acc);
+    const ReplayTo rp{nullptr, nullptr, nullptr};
+    const int wave = (int)(__builtin_amdgcn_readfirstlane(threadIdx.x) / 64), pairs = (int)(blockDim.x / 128);
+    const int pair = wave < pairs ? wave : wave - pairs;
+    const Feed feed{l_feed + (size_t)pair * kFeedBytes, flags, pair, pairs,
+                    ((uint64_t)blockIdx.x * (uint64_t)pairs + (uint64_t)pair) * 64};
+    if (wave < pairs) {
+        if (PREC == 0)
+            lanes_fp64<BIAS, TAB, ALLPOS, false, POT, true>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
+                                                            nullptr, rt, rp, nullptr, p.n_traj, p.traj_offset, feed);
+        else
+            lanes_fp32<BIAS, TAB, ALLPOS, false, true>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab), nullptr,
+                                                       rt, rp, nullptr, p.n_traj, p.traj_offset, feed);
+    } else {
+        if (PREC == 0)
+            feed_fp64(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(p.inst), p.traj_offset,
+                      feed);
+        else feed_fp32(p.inst, p.run, p.traj_offset, feed);
+    }
+    __syncthreads();
+    flush_lds_acc(acc, p.inst.acc);
+}
+
 // 2D noise, FP64 or FP32 state: a persistent grid over one instance.
 template <int PREC, int BIAS, bool ALLPOS, bool TIME>
 __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em2d_kernel(EmParams p)
@@ -1877,6 +2036,8 @@ __global__ void zero_words_kernel(unsigned long long *ptr, size_t n)
 }
 
 template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
+const void *pptr() { return reinterpret_cast<const void *>(&em_pair_kernel<PREC, BIAS, TAB, ALLPOS, POT>); }
+template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
 const void *kptr() { return reinterpret_cast<const void *>(&em_kernel<PREC, BIAS, TAB, ALLPOS, POT>); }
 template <int PREC, int BIAS, bool ALLPOS>
 const void *bptr() { return reinterpret_cast<const void *>(&batch_kernel<PREC, BIAS, ALLPOS>); }
@@ -1931,6 +2092,29 @@ const void *em_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_p
     else
         t = bias_kind == kBiasNone ? f1n.p : bias_kind == kBiasConst ? f1c.p : bias_kind == kBiasMlp ? f1m.p : f1x.p;
     return t[tm][all_pos ? 1 : 0];
+}
+
+template <int PREC, int BIAS, int POT>
+struct PTab {
+    const void *p[3][2] = {{pptr<PREC, BIAS, 0, false, POT>(), pptr<PREC, BIAS, 0, true, POT>()},
+                           {pptr<PREC, BIAS, 1, false, POT>(), pptr<PREC, BIAS, 1, true, POT>()},
+                           {pptr<PREC, BIAS, 2, false, POT>(), pptr<PREC, BIAS, 2, true, POT>()}};
+};
+
+const void *em_pair_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_pos, int pot_kind)
+{
+    static const PTab<0, kBiasNone, kPotGaussianBump> bn;
+    static const PTab<0, kBiasConst, kPotGaussianBump> bc;
+    static const PTab<0, kBiasNone, kPotPiecewiseLinear> dn;
+    static const PTab<0, kBiasConst, kPotPiecewiseLinear> dc;
+    static const PTab<1, kBiasNone, kPotPiecewiseLinear> fn;
+    static const PTab<1, kBiasConst, kPotPiecewiseLinear> fc;
+    if (bias_kind != kBiasNone && bias_kind != kBiasConst) return nullptr;
+    const bool c = bias_kind == kBiasConst;
+    const void *const(*t)[2] = pot_kind == kPotGaussianBump ? (c ? bc.p : bn.p)
+                               : precision == 0             ? (c ? dc.p : dn.p)
+                                                            : (c ? fc.p : fn.p);
+    return t[tab_mode][all_pos ? 1 : 0];
 }
 
 hipError_t em_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream, bool mlp_exact)
