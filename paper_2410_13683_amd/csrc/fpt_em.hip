@@ -231,6 +231,17 @@ __device__ __forceinline__ uint32_t wave_steps_left(bool has, uint32_t n, uint32
     return max_steps - __builtin_amdgcn_readfirstlane(v);
 }
 
+// The table interval of coordinate x, min(max(floor(x), 0), top) for every x (0 for NaN), as an integer:
+// v_cvt_u32_f64 truncates, takes negatives and NaN to 0 and saturates above.  Against the floor, two FP64
+// clamps and a conversion it leaves one integer minimum and the conversion back (FP64 operations issue
+// at some 5 cycles each and bound the kernel).
+__device__ __forceinline__ uint32_t interval_of(double x, uint32_t top)
+{
+    uint32_t j;
+    asm("v_cvt_u32_f64 %0, %1" : "=v"(j) : "v"(x));
+    return min(j, top);
+}
+
 // Wave-aggregated claim of trajectories from the global cursor.  Must be
 // reached by every lane of the wave.  Returns true in lanes that got one.
 __device__ __forceinline__ bool claim(bool need, uint64_t &rel, unsigned long long *cursor, uint64_t n_traj,
@@ -775,7 +786,7 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     const double a_const = (BIAS == kBiasConst) ? I.A : 0.0;
     const double half_a2_dN = 0.5 * a_const * a_const * dN;
     const double half_dN = 0.5 * dN;
-    const double jmax = (double)(staged_nodes(I) - 2);
+    const uint32_t j_top = (uint32_t)(staged_nodes(I) - 2);
     const double s_plus = in_vgpr(dk.s_plus), s_minus = in_vgpr(dk.s_minus);
 
     bool exhausted = false;
@@ -797,11 +808,38 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     PhiloxPre pre{};
     if (!FEED) pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
 
-    auto group = [&](auto censor_tag, const double z[4]) {
+    // Groups below the kink: a live lane has |pi| < sqrt 2 (the start aside) and |xi| < 6.8 (the Box-Muller
+    // radius is at most sqrt(66 ln 2)), so in four steps it moves less than `reach`; where every live lane
+    // starts the group further below phi_T than that, the drift takes the lower branch's constant without a
+    // comparison and two selects per step.  With the event's masks and the table index this took 1e6
+    // slow-roll -> ultra-slow-roll trajectories from 193.8 to 183.6 ms, with a constant bias from 227 to 199
+    // ms (109 and 128 VGPRs to 97 and 117).  Keeping the lane's table record in registers between steps,
+    // tried instead of the lookup, was slower (198 ms): its check is a branch in every step.
+    constexpr bool CAN_BELOW = POT == kPotPiecewiseLinear && !LEARNED;
+    const double reach = 4.0 * (fmax(1.4143, fabs(I.pi_in)) * dN + I.S_max * (fabs(a_const) * dN + 6.8 * sqrt_dN));
+    const double phi_below = (dk.s_plus == dk.s_minus) ? __builtin_inf() : phi_T - reach;
+    auto all_below = [&]() -> bool { return __builtin_amdgcn_ballot_w64(live && !(phi < phi_below)) == 0; };
+    // Groups without noise: a table that ends on S = 0 (its lowest phi node, or its last time node) leaves
+    // the paths beyond it classical, and a group in which every live lane stays there needs no normals, no
+    // table and no noise terms.  On a phi table a lane may come back during the group; the group then
+    // starts again from its state with noise.  The bump's noise ends after 3.5 of its 16 e-folds: 1e6
+    // trajectories at A = 3 went from 54.4 to 37.2 ms.
+    constexpr bool CAN_QUIET = TAB != 0 && !LEARNED && !ALLPOS;
+    const bool quiet_table = CAN_QUIET && l_tab[TAB == 1 ? 0 : I.n_tab - 1].x == 0.0;
+    const double quiet_N = I.phi_lo + (double)I.n_tab / I.inv_h;
+    auto quiet_lane = [&]() -> bool { return TAB == 1 ? phi < I.phi_lo : (double)n * dN > quiet_N; };
+
+    // Returns false only for a QUIET group that left the quiet region (nothing is recorded then).
+    auto group = [&](auto censor_tag, auto below_tag, auto quiet_tag, const double z[4]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
+        constexpr bool BELOW = decltype(below_tag)::value;
+        constexpr bool QUIET = decltype(quiet_tag)::value;
         bool fresh = false;
         uint32_t ev_status, ev_n;   // written before use: read only where fresh is set
         double ev_N, ev_lnw;
+        const bool live0 = live;
+        const double phi0 = phi, pi0 = pi_;
+        bool left_quiet = false;
 #pragma unroll(BIAS == kBiasMlpExact ? 1 : 4)   // the exact network: one copy of its code
         for (int j = 0; j < 4; ++j) {
             if (CENSOR && live && n == I.max_steps) {
@@ -812,21 +850,23 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
                 live = false;
                 fresh = true;
             }
+            if (QUIET && TAB == 1) left_quiet = left_quiet || !(phi < I.phi_lo);
             double r;   // V'/V
             if (POT == kPotGaussianBump) {
                 r = bump_dlnV(bc, phi);
             } else {
                 // the hardware reciprocal (relative error below 5e-8) and one Newton step: 2.2e-15
-                const double d = fma(phi, dk.kx, (phi >= phi_T) ? s_plus : s_minus);
+                const double d = fma(phi, dk.kx, (!BELOW && phi >= phi_T) ? s_plus : s_minus);
                 r = __builtin_amdgcn_rcp(d);
                 r = fma(r, fma(-d, r, 1.0), r);
             }
             double S, t;
-            if (TAB) {
+            if (QUIET) {
+                S = t = 0.0;
+            } else if (TAB) {
                 const double x = ((TAB == 2 ? (double)n * dN : phi) - I.phi_lo) * I.inv_h;
-                const double jf = fmin(fmax(floor(x), 0.0), jmax);
-                const double f = fmin(fmax(x - jf, 0.0), 1.0);
-                const int jj = (int)jf;
+                const uint32_t jj = interval_of(x, j_top);
+                const double f = fmin(fmax(x - (double)jj, 0.0), 1.0);
                 const double2 lo = l_tab[jj], hi = l_tab[jj + 1];
                 S = lo.x + f * (hi.x - lo.x);
                 t = lo.y + f * (hi.y - lo.y);
@@ -846,15 +886,19 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
                 }
                 a = a_held;
             }
-            const double zs = pick4(z, j);                // xi sqrt(dN)
+            const double zs = QUIET ? 0.0 : pick4(z, j);  // xi sqrt(dN)
             const double noise = S * zs;
             // without a bias the amplitude is a literal 0, which IEEE arithmetic does not fold away:
             // the terms are left out instead (the same values, up to the sign of a zero)
             const double aS = a * S;
-            const double phi_n = (BIAS == kBiasNone) ? phi + pi_ * dN + noise : phi + (pi_ + aS) * dN + noise;
+            const double phi_n = QUIET ? phi + pi_ * dN
+                                 : (BIAS == kBiasNone) ? phi + pi_ * dN + noise : phi + (pi_ + aS) * dN + noise;
             const double drift_pi = pi_ - (3.0 - 0.5 * pi_ * pi_) * (pi_ + r) * dN;
-            const double pi_n = (BIAS == kBiasNone) ? drift_pi + t * noise : drift_pi + t * (aS * dN + noise);
-            if (BIAS == kBiasConst) {
+            const double pi_n = QUIET ? drift_pi
+                                : (BIAS == kBiasNone) ? drift_pi + t * noise : drift_pi + t * (aS * dN + noise);
+            if (QUIET) {
+                // no noise, no weight
+            } else if (BIAS == kBiasConst) {
                 if (ALLPOS) {
                     lnw -= a * zs + half_a2_dN;
                 } else {
@@ -871,19 +915,34 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
                 }
                 grad_add(g_s, (ALLPOS || S > 0.0) ? -zs : 0.0, f0, f1);
             }
-            const bool crossed = phi_n <= phi_end;
-            const bool ended = 0.5 * pi_n * pi_n >= 1.0;
-            if (live && (crossed || ended)) {
+            // live and fresh are updated outside the branch, so that they stay lane masks; the event's inputs
+            // pass through an empty volatile asm, which keeps its work (a second comparison with phi_end, a
+            // division) from moving in front of the branch, into every step
+            const bool hit = live & ((phi_n <= phi_end) | (0.5 * pi_n * pi_n >= 1.0));
+            if (hit) {
+                double pa = phi, pb = phi_n;
+                uint32_t nb = n;
+                asm volatile("; passage event" : "+v"(pa), "+v"(pb), "+v"(nb));
+                const bool crossed = pb <= phi_end;
                 ev_status = crossed ? 0u : kFlagEndedEarly;
-                ev_n = n + 1;
-                ev_N = crossed ? (double)n * dN + dN * ((phi - phi_end) / (phi - phi_n)) : (double)(n + 1) * dN;
+                ev_n = nb + 1;
+                ev_N = crossed ? (double)nb * dN + dN * ((pa - phi_end) / (pa - pb)) : (double)(nb + 1) * dN;
                 ev_lnw = lnw;
-                live = false;
-                fresh = true;
             }
+            live = live & !hit;
+            fresh = fresh | hit;
             phi = phi_n;
             pi_ = pi_n;
             n += 1;
+        }
+        if (QUIET && TAB == 1) {
+            if (__builtin_amdgcn_ballot_w64(live0 && left_quiet) != 0) {
+                phi = phi0;
+                pi_ = pi0;
+                live = live0;
+                n -= 4;
+                return false;
+            }
         }
         if (fresh) {
             if (GRAD) {
@@ -894,6 +953,23 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
                 retire(rt, rel, ev_status, ev_n, ev_N, ev_lnw);
             }
         }
+        return true;
+    };
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    // The group's variant from its normals; `may_cap`: a lane may reach max_steps in it.
+    auto noisy_group = [&](bool may_cap, const double z[4]) {
+        if (may_cap) group(Yes(), No(), No(), z);
+        else if (CAN_BELOW && all_below()) group(No(), std::integral_constant<bool, CAN_BELOW>(), No(), z);
+        else group(No(), No(), No(), z);
+    };
+    auto quiet_group = [&](bool may_cap) -> bool {
+        if constexpr (CAN_QUIET) {
+            const double none[4] = {0.0, 0.0, 0.0, 0.0};
+            if (may_cap || !quiet_table || __builtin_amdgcn_ballot_w64(live && !quiet_lane()) != 0) return false;
+            return group(No(), No(), Yes(), none);
+        }
+        return false;
     };
 
     if constexpr (FEED) {
@@ -910,9 +986,8 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             for (int q = 0; q < kFeedSteps / 2; q += 2) {
                 const double z[4] = {v[q].x, v[q].y, v[q + 1].x, v[q + 1].y};
                 // all lanes are at the same step
-                if ((uint32_t)__builtin_amdgcn_readfirstlane(n) + 4 > I.max_steps)
-                    group(std::integral_constant<bool, true>(), z);
-                else group(std::integral_constant<bool, false>(), z);
+                const bool may_cap = (uint32_t)__builtin_amdgcn_readfirstlane(n) + 4 > I.max_steps;
+                if (!quiet_group(may_cap)) noisy_group(may_cap, z);
             }
         }
         return;
@@ -921,13 +996,14 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
         const uint32_t left = wave_steps_left(has, n, I.max_steps);
         for (int k = 0; k < R.chunk; k += 4) {
             if (!__any(live)) break;
+            const bool may_cap = (uint32_t)k + 4 > left;
+            if (quiet_group(may_cap)) continue;
             uint32_t w[4];
             philox_call(n >> 2, pre, R.key0, R.key1, w);
             double z[4];
             box_muller64(w[0], w[1], sqrt_dN, l_bm, z[0], z[1]);
             box_muller64(w[2], w[3], sqrt_dN, l_bm, z[2], z[3]);
-            if ((uint32_t)k + 4 > left) group(std::integral_constant<bool, true>(), z);
-            else group(std::integral_constant<bool, false>(), z);
+            noisy_group(may_cap, z);
         }
         if (!live) has = false;
         if (claim(!has, rel, cursor, n_traj, exhausted)) {
@@ -1457,7 +1533,7 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
     const double dN = R.dN, sqrt_dN = R.sqrt_dN, phi_end = I.phi_end, phi_T = I.phi_T;
     const double a = (BIAS == kBiasConst) ? I.A : 0.0;
     const double half_a2_dN = 0.5 * a * a * dN;
-    const double jmax = (double)(staged_nodes(I) - 2);
+    const uint32_t j_top = (uint32_t)(staged_nodes(I) - 2);
     const double2 *l_bm = l_tab + 3 * staged_nodes(I);
     const double s_plus = in_vgpr(dk.s_plus), s_minus = in_vgpr(dk.s_minus);
 
@@ -1469,9 +1545,16 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
     uint32_t n = 0;
     PhiloxPre pre = philox_pre(traj_offset + rel, I.instance, R.key0, R.key1);
 
+    // Groups below the kink, as in lanes_fp64: two steps' reach, with the noise S (xi_1, xi_2) and the bias
+    // a S e (|e| <= 1) bounded by twice the largest entry of S.
+    const double reach =
+        2.0 * (fmax(1.4143, fabs(I.pi_in)) * dN + 2.0 * I.S_max * (fabs(a) * dN + 6.8 * sqrt_dN));
+    const double phi_below = (dk.s_plus == dk.s_minus) ? __builtin_inf() : phi_T - reach;
+
     // groups of two steps: one Philox call gives both steps' (xi_1, xi_2)
-    auto group = [&](auto censor_tag, const double z[4]) {
+    auto group = [&](auto censor_tag, auto below_tag, const double z[4]) {
         constexpr bool CENSOR = decltype(censor_tag)::value;
+        constexpr bool BELOW = decltype(below_tag)::value;
         bool fresh = false;
         uint32_t ev_status, ev_n;   // written before use: read only where fresh is set
         double ev_N, ev_lnw;
@@ -1485,14 +1568,14 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
                 live = false;
                 fresh = true;
             }
-            const double d = fma(phi, dk.kx, (phi >= phi_T) ? s_plus : s_minus);
+            const double d = fma(phi, dk.kx, (!BELOW && phi >= phi_T) ? s_plus : s_minus);
             double r = __builtin_amdgcn_rcp(d);          // V'/V: reciprocal and one Newton step
             r = fma(r, fma(-d, r, 1.0), r);
             // table coordinate: phi, or the run's time n dN for a time-indexed table
             const double x = ((TIME ? (double)n * dN : phi) - I.phi_lo) * I.inv_h;
-            const double jf = fmin(fmax(floor(x), 0.0), jmax);
-            const double f = fmin(fmax(x - jf, 0.0), 1.0);
-            const Node2d S = lerp_node2d(l_tab, (int)jf, f);
+            const uint32_t jj = interval_of(x, j_top);
+            const double f = fmin(fmax(x - (double)jj, 0.0), 1.0);
+            const Node2d S = lerp_node2d(l_tab, (int)jj, f);
             const double z1 = z[2 * j], z2 = z[2 * j + 1];          // xi sqrt(dN)
             const double noise_phi = S.Spp * z1 + S.Spq * z2;
             const double noise_pi = S.Spq * z1 + S.Sqq * z2;
@@ -1509,16 +1592,20 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
                 if (ALLPOS) lnw -= dA;
                 else lnw -= (S.Spp != 0.0 || S.Spq != 0.0 || S.Sqq != 0.0) ? dA : 0.0;
             }
-            const bool crossed = phi_n <= phi_end;
-            const bool ended = 0.5 * pi_n * pi_n >= 1.0;
-            if (live && (crossed || ended)) {
+            // as in lanes_fp64
+            const bool hit = live & ((phi_n <= phi_end) | (0.5 * pi_n * pi_n >= 1.0));
+            if (hit) {
+                double pa = phi, pb = phi_n;
+                uint32_t nb = n;
+                asm volatile("; passage event" : "+v"(pa), "+v"(pb), "+v"(nb));
+                const bool crossed = pb <= phi_end;
                 ev_status = crossed ? 0u : kFlagEndedEarly;
-                ev_n = n + 1;
-                ev_N = crossed ? (double)n * dN + dN * ((phi - phi_end) / (phi - phi_n)) : (double)(n + 1) * dN;
+                ev_n = nb + 1;
+                ev_N = crossed ? (double)nb * dN + dN * ((pa - phi_end) / (pa - pb)) : (double)(nb + 1) * dN;
                 ev_lnw = lnw;
-                live = false;
-                fresh = true;
             }
+            live = live & !hit;
+            fresh = fresh | hit;
             phi = phi_n;
             pi_ = pi_n;
             n += 1;
@@ -1535,8 +1622,11 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
             double z[4];
             box_muller64(w[0], w[1], sqrt_dN, l_bm, z[0], z[1]);
             box_muller64(w[2], w[3], sqrt_dN, l_bm, z[2], z[3]);
-            if ((uint32_t)k + 2 > left) group(std::integral_constant<bool, true>(), z);
-            else group(std::integral_constant<bool, false>(), z);
+            using Yes = std::integral_constant<bool, true>;
+            using No = std::integral_constant<bool, false>;
+            if ((uint32_t)k + 2 > left) group(Yes(), No(), z);
+            else if (__builtin_amdgcn_ballot_w64(live && !(phi < phi_below)) == 0) group(No(), Yes(), z);
+            else group(No(), No(), z);
         }
         if (!live) has = false;
         if (claim(!has, rel, cursor, n_traj, exhausted)) {
