@@ -690,8 +690,13 @@ extern "C" int fpt_create(const fpt_potential *pot, const fpt_noise_table *table
     I.noise_dim = dim;
     I.tab64_2d = reinterpret_cast<const double2 *>(base + off_tab2d);
     I.tab32_2d = reinterpret_cast<const float4 *>(base + off_tab2d32);
-    I.S_max = 0.0;
-    for (int i = 0; i < nt && dim == 1; ++i) I.S_max = std::max(I.S_max, table->S[i]);
+    I.n_pos = 0;
+    while (dim == 1 && I.n_pos < nt && h32[4 * (size_t)I.n_pos] > 0.0f) ++I.n_pos;
+    I.S_max = I.t_max = 0.0;
+    for (int i = 0; i < nt && dim == 1; ++i) {
+        I.S_max = std::max(I.S_max, table->S[i]);
+        I.t_max = std::max(I.t_max, std::fabs(table->tan_theta[i]));
+    }
     for (size_t i = 0; i < h2d.size(); ++i)
         if (i % 6 < 3) I.S_max = std::max(I.S_max, std::fabs(h2d[i]));
     I.all_S_pos = all_pos ? 1 : 0;

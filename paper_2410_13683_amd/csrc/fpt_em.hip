@@ -1205,11 +1205,38 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             pi_safe = fmaf(-16.8f, delta, 1.4128f);
     }
 
+    // Time tables: a group is plain for a lane that stays below the kink (as in lanes_fp64, 16 steps' reach,
+    // 1 % above it for the rounding), whose coordinate runs inside [0, last node before the first one with
+    // S = 0], and that cannot reach |pi| = sqrt 2 (pi_safe's bound with the largest S and tan theta of the
+    // table and the largest |V'/V| between phi_end and the kink, where it is monotonic): its steps need no
+    // clamp, no branch select, no test of S and no end test, and n + j is exact in FP32.  Eight operations
+    // fewer of some fifty per step: 1e6 trajectories of the time-indexed problem 124.5 -> 104.8 ms.
+    const float z_most = fmaf(6.8f, __builtin_amdgcn_sqrtf(c.dN), fabsf((float)A) * c.dN);
+    const float reach = 1.01f * 16.0f * fmaf((float)I.S_max, z_most, fmaxf(1.4143f, fabsf((float)I.pi_in)) * c.dN);
+    const float below = (c.s_plus == c.s_minus) ? __builtin_inff() : -reach;
+    const float u_plain = (float)(I.n_pos - 1);
+    float pi_plain = -1.0f;
+    if (TAB == 2) {
+        const float d_end = fmaf(-(c.xT_hi + c.xT_lo), c.kx, c.s_minus);
+        const float r_most = 1.01f / fminf(fabsf(c.s_minus), fabsf(d_end));
+        const float delta = fmaf(6.0f, fmaf(0.7072f, c.dN, r_most), (float)(I.t_max * I.S_max) * z_most);
+        if (delta >= 0.0f && delta < 1.0f) pi_plain = fmaf(-16.8f, delta, 1.4128f);
+    }
+    auto plain_lane = [&]() -> bool {
+        const float u0 = fmaf((float)n, c.t_scale, c.t_off), u1 = fmaf((float)(n + G - 1), c.t_scale, c.t_off);
+        return u0 >= 0.0f && u1 < u_plain && n < (1u << 24) - G &&
+               (xh - c.xT_hi) + (xl - c.xT_lo) < below && fabsf(ps) <= pi_plain;
+    };
+
     auto group = [&](auto censor_tag, auto span_tag, auto end_tag, const float z[G]) {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool SPAN = decltype(span_tag)::value;
         constexpr bool END = decltype(end_tag)::value;   // test the eps_1 = 1 end in each step
-        static_assert(!SPAN || (TAB == 1 && !CENSOR), "one record per group: phi tables, no censoring");
+        static_assert(!SPAN || (TAB != 0 && !CENSOR), "one record per group, or a plain time group: no censoring");
+        // a SPAN group of a time table is plain: below the kink, inside the table, S > 0 (plain_lane)
+        constexpr bool PLAIN = TAB == 2 && SPAN;
+        constexpr bool ON = ALLPOS || PLAIN;                      // S > 0 in every step
+        const float nf = PLAIN ? (float)n : 0.0f;
         // the rounded sum xs is read by a step only for a per-step table lookup and by the control
         constexpr bool STEP_XS = LEARNED || (TAB == 1 && !SPAN);
         float zacc = 0.0f;        // constant bias: sum of this group's xi sqrt(dN); learned: of its dA
@@ -1218,7 +1245,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         double ev_N, ev_lnw;
         auto lnw_now = [&](uint32_t steps) -> double {
             if (LEARNED) return lnw - (double)zacc;
-            return lnw_of(zsum + (double)zacc, ALLPOS ? steps : n_on);
+            return lnw_of(zsum + (double)zacc, ALLPOS ? steps : PLAIN ? n_on + (steps - n) : n_on);
         };
 #pragma unroll(BIAS == kBiasMlpExact ? 1 : G)   // the exact network: one copy of its code
         for (int j = 0; j < G; ++j) {
@@ -1233,12 +1260,13 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             // (V'/V) dN/2 exactly: 1/(kx (phi - phi_T) + s), phi - phi_T = (xh - xT_hi) + (xl - xT_lo)
             auto drift_exact = [&]() -> float {
                 const float dT = (xh - c.xT_hi) + (xl - c.xT_lo);
-                return __builtin_amdgcn_rcpf(fmaf(dT, c.kx, (dT >= 0.0f) ? s_plus : s_minus));
+                return __builtin_amdgcn_rcpf(fmaf(dT, c.kx, (!PLAIN && dT >= 0.0f) ? s_plus : s_minus));
             };
             float S, t, r;        // r = (V'/V) dN/2
             if (TAB == 2) {
                 // time table: the node at n dN; V'/V exactly (the V'/V intervals follow phi)
-                const float u = __builtin_amdgcn_fmed3f(fmaf((float)(n + j), c.t_scale, c.t_off), 0.0f, c.jtop);
+                const float u = PLAIN ? fmaf(nf + (float)j, c.t_scale, c.t_off)     // n + j < 2^24: exact
+                                      : __builtin_amdgcn_fmed3f(fmaf((float)(n + j), c.t_scale, c.t_off), 0.0f, c.jtop);
                 const float f = __builtin_amdgcn_fractf(u);
                 const float4 node = l_tab[(int)u];
                 S = fmaf(f, node.y, node.x);
@@ -1298,7 +1326,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             // rides in z = xi sqrt(dN) + a dN; the learned one is added here, z = xi sqrt(dN))
             const float Bn = S * (LEARNED ? fmaf(a, c.dN, zj) : zj);
             if (BIAS == kBiasConst) {
-                if (ALLPOS) {
+                if (ON) {
                     zacc = (j == 0) ? z[0] : zacc + zj;
                 } else {
                     const bool on = S > 0.0f;
@@ -1353,6 +1381,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             fresh = fresh || hit;
         }
         n += G;
+        if (PLAIN && !ALLPOS && BIAS == kBiasConst) n_on += G;
         if (LEARNED) lnw -= (double)zacc;
         else zsum += (double)zacc;
         if (fresh) {
@@ -1404,6 +1433,9 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
                         group(F(), T(), F(), z);
                     else group(F(), T(), T(), z);
                 }
+            } else if constexpr (TAB == 2) {
+                if (__builtin_amdgcn_ballot_w64(live && !plain_lane()) == 0) group(F(), T(), F(), z);
+                else group(F(), F(), T(), z);
             } else {
                 group(F(), F(), T(), z);
             }

@@ -65,6 +65,8 @@ struct Inst {
     // a group evaluating one record for all its steps can read (all 0 without a smooth record)
     float rec_S, rec_dS, rec_t, rec_dt, rec_r, rec_dr;
     double S_max;                    // the largest S_j (1D noise) or entry of a node's square root (2D)
+    double t_max;                    // the largest |tan theta_j| (1D noise)
+    int32_t n_pos;                   // 1D noise: leading nodes with S_j > 0 in FP32
     int32_t all_S_pos;               // every node has S > 0 (the ln w update needs no test)
     // 2D noise (noise_dim == 2): node j is (S_pp, S_pq), (S_qq, e_phi), (e_pi, 0) -- the symmetric
     // square root of the node covariance and its unit principal axis
