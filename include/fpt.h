@@ -436,7 +436,10 @@ int fpt_noise_table_bessel2d_time(const fpt_potential *pot, double sigma, int32_
  * any instance that still has trajectories.  Results are identical to fpt_run
  * on each context with the same seed and trajectory range.  The launch is
  * captured in a hipGraph on the first run on a (non-null) stream and replayed
- * afterwards with the new work list, seed and dN.  The contexts must share the
+ * afterwards with the new work list, seed and dN.  A small batch (with the default
+ * block size: at most 512 trajectories per compute unit, counting each instance's
+ * in whole blocks) is launched directly instead, each block on a slice of one
+ * instance of its own.  The contexts must share the
  * device and the precision; NONE and CONST biases may be mixed; MLP is not
  * supported here.  Per-trajectory outputs are not produced. */
 typedef struct fpt_batch fpt_batch;

@@ -1974,41 +1974,63 @@ em_kernel(EmParams p)
     flush_lds_acc(acc, p.inst.acc);
 }
 
-// Paired waves: one trajectory per lane of the block's first half of waves, the second half forming
-// their normals (see Feed).  The grid covers the trajectories; p.cursor is not used.
+// One block of paired waves (see Feed): trajectories traj_offset + first .. of instance I, one per lane of
+// the block's first half of waves, of n_traj in all; the second half forms their normals.
+template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT>
+__device__ __forceinline__ void pair_block(const Inst &I, const RunArgs &R, unsigned char *smem, uint32_t *flags,
+                                           double *d_N, double *d_lnw, uint32_t *d_steps, uint64_t n_traj,
+                                           uint64_t traj_offset, uint64_t first)
+{
+    const LdsAcc acc = lds_acc(smem, I.hist.n_bins);
+    unsigned char *l_tab = smem + align16(acc_bytes(I.hist.n_bins));
+    unsigned char *l_feed = l_tab + tab_bytes(PREC, I.n_tab);
+    zero_lds_acc(acc);
+    if (PREC == 0) stage_table64(I, reinterpret_cast<double2 *>(l_tab));
+    else stage_table32(I, reinterpret_cast<float4 *>(l_tab), (float)R.dN);
+    __syncthreads();
+    const RetireTo rt{d_N, d_lnw, d_steps, acc.cnt, acc.sum, acc.nb, I.hist};
+    const ReplayTo rp{nullptr, nullptr, nullptr};
+    const int wave = (int)(__builtin_amdgcn_readfirstlane(threadIdx.x) / 64), pairs = (int)(blockDim.x / 128);
+    const int pair = wave < pairs ? wave : wave - pairs;
+    const Feed feed{l_feed + (size_t)pair * kFeedBytes, flags, pair, pairs, first + (uint64_t)pair * 64};
+    if (wave < pairs) {
+        if (PREC == 0)
+            lanes_fp64<BIAS, TAB, ALLPOS, false, POT, true>(I, R, reinterpret_cast<const double2 *>(l_tab), nullptr,
+                                                            rt, rp, nullptr, n_traj, traj_offset, feed);
+        else
+            lanes_fp32<BIAS, TAB, ALLPOS, false, true>(I, R, reinterpret_cast<const float4 *>(l_tab), nullptr, rt, rp,
+                                                       nullptr, n_traj, traj_offset, feed);
+    } else {
+        if (PREC == 0)
+            feed_fp64(I, R, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(I), traj_offset, feed);
+        else feed_fp32(I, R, traj_offset, feed);
+    }
+    __syncthreads();
+    flush_lds_acc(acc, I.acc);
+}
+
+// A run on paired waves.  The grid covers the trajectories; p.cursor is not used.
 template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
 __global__ void __launch_bounds__(64 * 2 * kFeedMaxPairs) em_pair_kernel(EmParams p)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t flags[2 * kFeedMaxPairs];
-    const LdsAcc acc = lds_acc(smem, p.inst.hist.n_bins);
-    unsigned char *l_tab = smem + align16(acc_bytes(p.inst.hist.n_bins));
-    unsigned char *l_feed = l_tab + tab_bytes(PREC, p.inst.n_tab);
-    zero_lds_acc(acc);
-    if (PREC == 0) stage_table64(p.inst, reinterpret_cast<double2 *>(l_tab));
-    else stage_table32(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
-    __syncthreads();
-    const RetireTo rt = retire_to(p, acc);
-    const ReplayTo rp{nullptr, nullptr, nullptr};
-    const int wave = (int)(__builtin_amdgcn_readfirstlane(threadIdx.x) / 64), pairs = (int)(blockDim.x / 128);
-    const int pair = wave < pairs ? wave : wave - pairs;
-    const Feed feed{l_feed + (size_t)pair * kFeedBytes, flags, pair, pairs,
-                    ((uint64_t)blockIdx.x * (uint64_t)pairs + (uint64_t)pair) * 64};
-    if (wave < pairs) {
-        if (PREC == 0)
-            lanes_fp64<BIAS, TAB, ALLPOS, false, POT, true>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
-                                                            nullptr, rt, rp, nullptr, p.n_traj, p.traj_offset, feed);
-        else
-            lanes_fp32<BIAS, TAB, ALLPOS, false, true>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab), nullptr,
-                                                       rt, rp, nullptr, p.n_traj, p.traj_offset, feed);
-    } else {
-        if (PREC == 0)
-            feed_fp64(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(p.inst), p.traj_offset,
-                      feed);
-        else feed_fp32(p.inst, p.run, p.traj_offset, feed);
-    }
-    __syncthreads();
-    flush_lds_acc(acc, p.inst.acc);
+    pair_block<PREC, BIAS, TAB, ALLPOS, POT>(p.inst, p.run, smem, flags, p.d_N, p.d_lnw, p.d_steps, p.n_traj,
+                                             p.traj_offset, (uint64_t)blockIdx.x * (blockDim.x / 2));
+}
+
+// A batch on paired waves: block b runs the slice items[b] of its instance, at most one trajectory per
+// lane of its integrating waves.
+template <int PREC, int BIAS, bool ALLPOS>
+__global__ void __launch_bounds__(64 * 2 * kFeedMaxPairs) batch_pair_kernel(const Inst *insts, const WorkItem *items,
+                                                                            RunArgs run)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t flags[2 * kFeedMaxPairs];
+    const WorkItem W = items[blockIdx.x];
+    const Inst I = insts[W.inst];
+    pair_block<PREC, BIAS, 1, ALLPOS, kPotPiecewiseLinear>(I, run, smem, flags, nullptr, nullptr, nullptr, W.count,
+                                                           W.begin, 0);
 }
 
 // 2D noise, FP64 or FP32 state: a persistent grid over one instance.
@@ -2308,6 +2330,24 @@ const void *batch_kernel_ptr(int precision, int bias_kind, bool all_pos)
         {{bptr<1, kBiasNone, false>(), bptr<1, kBiasNone, true>()},
          {bptr<1, kBiasConst, false>(), bptr<1, kBiasConst, true>()}}};
     return t[precision ? 1 : 0][bias_kind == kBiasNone ? 0 : 1][all_pos ? 1 : 0];
+}
+
+template <int PREC, int BIAS, bool ALLPOS>
+const void *bpptr() { return reinterpret_cast<const void *>(&batch_pair_kernel<PREC, BIAS, ALLPOS>); }
+
+hipError_t batch_pair_launch(int precision, int bias_kind, bool all_pos, const Inst *insts, const WorkItem *items,
+                             const RunArgs &run, int max_bins, int max_tab, int grid, int pairs, hipStream_t stream)
+{
+    static const void *const t[2][2][2] = {
+        {{bpptr<0, kBiasNone, false>(), bpptr<0, kBiasNone, true>()},
+         {bpptr<0, kBiasConst, false>(), bpptr<0, kBiasConst, true>()}},
+        {{bpptr<1, kBiasNone, false>(), bpptr<1, kBiasNone, true>()},
+         {bpptr<1, kBiasConst, false>(), bpptr<1, kBiasConst, true>()}}};
+    const void *fn = t[precision ? 1 : 0][bias_kind == kBiasNone ? 0 : 1][all_pos ? 1 : 0];
+    RunArgs r = run;
+    void *args[] = {&insts, &items, &r};
+    return hipLaunchKernel(fn, dim3(grid), dim3(128 * pairs), args,
+                           em_lds_bytes(max_bins, max_tab, precision, 0) + pairs * kFeedBytes, stream);
 }
 
 hipError_t batch_launch(int precision, int bias_kind, bool all_pos, const Inst *insts, const WorkItem *items,

@@ -174,6 +174,10 @@ const void *batch_kernel_ptr(int precision, int bias_kind, bool all_pos);
 hipError_t batch_launch(int precision, int bias_kind, bool all_pos, const Inst *insts, const WorkItem *items,
                         const BatchRun *run, unsigned long long *cursors, int max_bins, int max_tab, int grid,
                         int block, hipStream_t stream);
+// A batch on paired waves: grid blocks of `pairs` pairs, block b running items[b], a slice of at most
+// 64 pairs trajectories.
+hipError_t batch_pair_launch(int precision, int bias_kind, bool all_pos, const Inst *insts, const WorkItem *items,
+                             const RunArgs &run, int max_bins, int max_tab, int grid, int pairs, hipStream_t stream);
 hipError_t zero_words(unsigned long long *ptr, size_t n, hipStream_t stream);
 
 // Learned-control kernels (fpt_mlp.hip).  params: 4482 FP32 values,

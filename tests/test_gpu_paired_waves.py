@@ -88,3 +88,47 @@ def test_step_cap_inside_a_turn(problem, cap):
     for u, v in zip(x, y):
         np.testing.assert_array_equal(u, v)
     assert hx["n_censored"] == hy["n_censored"] and (cap > 100 or hx["n_censored"] > 0)
+
+
+def _batch_counts(pairs, cus):
+    """Counts that just fit `pairs` pairs per block on one block per CU, ragged slices among them."""
+    lanes = 64 * pairs
+    counts = [1, 0, lanes - 1, lanes, lanes + 1, 63]
+    used = sum(-(-n // lanes) for n in counts)
+    return counts + [(cus - used) * lanes - 5]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("pairs", [1, 2, 3, 4, 6, 8, 9])
+def test_small_batch_equals_single_runs(precision, pairs):
+    """Batches at the counts where the pairs per block change, and one past the last (9: the general
+    kernel): per instance the counts, flags and step total of its own run."""
+    from paper_2410_13683_amd import fpt
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    counts = _batch_counts(pairs, cus)
+    ws = [_is(W.srusr_bessel(), (0.0, 1.0)[i % 2]).with_(precision=precision, phi_end=-0.01 - 0.004 * i,
+                                                          dN=2e-3, max_steps=2500, extra={"instance": i})
+          for i in range(len(counts))]
+    print(f"small batch precision={precision} pairs={pairs} total={sum(counts)}", flush=True)
+    ctxs = [gpu_context(w) for w in ws]
+    stream = torch.cuda.Stream()
+    batch = fpt.Batch(ctxs, use_graph=True)
+    off = (1 << 32) - 100
+    for _ in range(2):                       # twice: new work lists on the same batch
+        for c in ctxs:
+            c.reset()
+        batch.run(np.array(counts, dtype=np.uint64), ws[0].dN, ws[0].seed, off, stream=stream)
+        hb = [c.histogram() for c in ctxs]
+    for i, (w, n) in enumerate(zip(ws, counts)):
+        one = gpu_context(w, block_size=256, blocks_per_cu=2)
+        if n:
+            one.run(n, w.dN, w.seed, off)
+        h = one.histogram()
+        one.destroy()
+        np.testing.assert_array_equal(hb[i]["count"], h["count"])
+        for k in ("n_traj", "n_censored", "n_ended_early", "n_steps_total"):
+            assert hb[i][k] == h[k], (i, k)
+        np.testing.assert_allclose(hb[i]["sum_lnw2"], h["sum_lnw2"], rtol=1e-12, atol=0)
+    batch.destroy()
+    for c in ctxs:
+        c.destroy()
