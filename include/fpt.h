@@ -294,9 +294,11 @@ int fpt_mlp_table(fpt_ctx *ctx, double *a_out);
  *   dJ/dtheta = (1/n) sum_T w^2 sum_k (-xi_k sqrt(dN)) da(x_k)/dtheta,
  * the on-policy value of the replay gradient of E_old[w_old w_theta 1_T]
  * (minimising J minimises the log-weight variance on the tail under the
- * lognormal weight model of Sec. 4.1).  Tail trajectories are integrated again
- * (replayed from their counter-based random numbers) to accumulate the
- * grid-node weights G_c = (1/n) sum_T w^2 sum_k (-xi_k sqrt(dN)) beta_c(x_k),
+ * lognormal weight model of Sec. 4.1).  Up to 2^19 trajectories, each path's
+ * sums over the steps in a grid cell are recorded as it is sampled; otherwise, and
+ * for paths that visit more cells than there is room for, tail trajectories are
+ * integrated again (replayed from their counter-based random numbers).  Both
+ * accumulate the grid-node weights G_c = (1/n) sum_T w^2 sum_k (-xi_k sqrt(dN)) beta_c(x_k),
  * which are propagated through the network at the nodes.  objective
  * FPT_MLP_OBJ_J gives dJ/dtheta; FPT_MLP_OBJ_LOG_J gives d ln J/dtheta =
  * (dJ/dtheta)/J (J divided out on the device), whose scale does not depend on
@@ -306,8 +308,10 @@ int fpt_mlp_table(fpt_ctx *ctx, double *a_out);
  * T), d_G (device, grid_n[0] grid_n[1]
  * doubles, or NULL), J_out and n_tail_out (host, or NULL; if either is given
  * the call waits for the device).  Asynchronous on hip_stream otherwise;
- * device scratch of about 36 bytes per trajectory (at most 2^22 at a time) is
- * allocated on first use and kept.  Errors: FPT_EINVAL, FPT_ENOMEM, FPT_EHIP. */
+ * device scratch of about 36 bytes per trajectory (at most 2^22 at a time) and, up
+ * to 2^19 trajectories, of the records (n0 + n1 + 64 cells per trajectory, at most
+ * 256, at 18 bytes in FP32 and 34 in FP64 state) is allocated on first use and kept;
+ * where there is no memory for the records, the tail is replayed.  Errors: FPT_EINVAL, FPT_ENOMEM, FPT_EHIP. */
 enum { FPT_MLP_OBJ_J = 0, FPT_MLP_OBJ_LOG_J = 1 };
 int fpt_mlp_grad(fpt_ctx *ctx, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset, double tail_lo,
                  int32_t objective, void *hip_stream, float *d_grad, double *d_G, double *J_out,

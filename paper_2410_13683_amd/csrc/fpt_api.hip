@@ -335,6 +335,9 @@ struct fpt_ctx {
     // per-trajectory scratch of gradient runs, grown on demand
     void *d_scratch = nullptr;
     size_t scratch_cap = 0;
+    // records of gradient runs of up to kRecordMax trajectories, grown on demand
+    void *d_rec = nullptr;
+    size_t rec_bytes = 0;
 };
 
 static const size_t kGradSlice = size_t(1) << 22;
@@ -925,6 +928,7 @@ extern "C" void fpt_destroy(fpt_ctx *c)
     if (c->d_mem) (void)hipFree(c->d_mem);
     if (c->d_mlp) (void)hipFree(c->d_mlp);
     if (c->d_scratch) (void)hipFree(c->d_scratch);
+    if (c->d_rec) (void)hipFree(c->d_rec);
     delete c;
 }
 
@@ -994,12 +998,57 @@ static int mlp_grad_check(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t traj_
     return FPT_OK;
 }
 
+// Up to this many trajectories a gradient run records each path's sums per visited cell while it samples
+// (em_record_kernel) and weighs the tail's records afterwards (tail_weigh_kernel), instead of integrating
+// the tail's paths a second time: 250,000 trajectories, most of them in T, take 42 instead of 76 ms.  A
+// path makes a record per cell it leaves (57 to 59 on slow roll -> ultra-slow roll with 32 x 32 nodes);
+// the pool has room for n0 + n1 + 64 (at 18 bytes in FP32 state, 2.3 KB per trajectory there), and a
+// path that makes more is replayed.  Beyond, the pool would take gigabytes, or the sampling be cut into
+// launches that no longer fill the GPU through their ends.
+static const size_t kRecordMax = size_t(1) << 19;
+
+static uint32_t record_cap(const GridSpec &g) { return (uint32_t)std::min(g.n0 + g.n1 + 64, 256); }
+
+// The record pool for n trajectories in the context's memory (grown if need be, which a stream being
+// captured forbids); false if there is none.
+static bool record_pool(fpt_ctx *c, uint64_t n, hipStream_t s, RecordPool &rec)
+{
+    if (n > kRecordMax) return false;
+    rec.cap = record_cap(c->grid);
+    const size_t n_rec = (size_t)n * rec.cap, sums = n_rec * (c->precision == FPT_FP64 ? 32 : 16);
+    const size_t bytes = sums + n_rec * sizeof(uint16_t) + (size_t)n * sizeof(uint32_t) + 64;
+    if (bytes > c->rec_bytes) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (c->d_rec) {
+            if (hipDeviceSynchronize() != hipSuccess || hipFree(c->d_rec) != hipSuccess) return false;
+            c->d_rec = nullptr;
+            c->rec_bytes = 0;
+        }
+        if (hipMalloc(&c->d_rec, bytes) != hipSuccess) {
+            c->d_rec = nullptr;
+            (void)hipGetLastError();      // not an error of the call: the tail is replayed instead
+            return false;
+        }
+        c->rec_bytes = bytes;
+    }
+    unsigned char *p = static_cast<unsigned char *>(c->d_rec);
+    rec.sums = p;
+    rec.count = reinterpret_cast<uint32_t *>(p + sums);
+    rec.cell = reinterpret_cast<uint16_t *>(rec.count + n);
+    return true;
+}
+
 // The gradient run of fpt_mlp_grad on per-trajectory scratch sb of cap trajectories (N, ln w, steps
 // and a tail entry each, 36 bytes): slices of at most cap trajectories are integrated, their tail
-// compacted and replayed, then the node weights are propagated through the network.
+// weighed from its records (rec, one slice only) or compacted and replayed, then the node weights are
+// propagated through the network.
 static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset, double tail_lo,
                         int32_t objective, hipStream_t s, float *d_grad, double *d_G, double *J_out,
-                        uint64_t *n_tail_out, unsigned char *sb, size_t cap)
+                        uint64_t *n_tail_out, unsigned char *sb, size_t cap, const RecordPool *rec = nullptr)
 {
     int rc = FPT_OK;
     TailEntry *d_tail = reinterpret_cast<TailEntry *>(sb);
@@ -1029,7 +1078,8 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
     const int block = c->opt.block_size ? c->opt.block_size : 1024;
     int grid_rp = 0;
     const int n_cells = grid_cells(c->inst);
-    const void *em_fn = em_kernel_ptr(c->precision, kBiasMlp, tab_mode(c->inst), c->inst.all_S_pos != 0);
+    const void *em_fn = rec ? em_record_kernel_ptr(c->precision, tab_mode(c->inst), c->inst.all_S_pos != 0)
+                            : em_kernel_ptr(c->precision, kBiasMlp, tab_mode(c->inst), c->inst.all_S_pos != 0);
     const size_t em_lds = em_lds_bytes(c->opt.n_bins, c->inst.n_tab, c->precision, n_cells);
     rc = occupancy_grid(replay_kernel_ptr(c->precision, c->inst.all_S_pos != 0), block,
                         replay_lds_bytes(c->inst.n_tab, c->precision, n_cells, (int)n_nodes), c->cu_count,
@@ -1054,9 +1104,15 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
         int grid_em = 0, block_em = 0;
         rc = run_shape(c, em_fn, em_lds, m, grid_em, block_em);
         if (rc) return rc;
-        HIP_TRY(em_launch(p, c->precision, grid_em, block_em, s));
-        HIP_TRY(mlp_tail_compact(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, d_tail, &cnt[0],
-                                 &cnt[1], c->d_J, s));
+        if (rec) {
+            HIP_TRY(em_record_launch(p, *rec, c->precision, grid_em, block_em, s));
+            HIP_TRY(tail_weigh(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, *rec, c->precision,
+                               g.n0, g.n1, c->d_G, d_tail, &cnt[0], &cnt[1], c->d_J, c->cu_count, s));
+        } else {
+            HIP_TRY(em_launch(p, c->precision, grid_em, block_em, s));
+            HIP_TRY(mlp_tail_compact(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, d_tail,
+                                     &cnt[0], &cnt[1], c->d_J, s));
+        }
         HIP_TRY(replay_launch(rp, c->precision, grid_rp, block, s));
     }
     // d_J holds sum_T w^2 = n J: dividing G by it gives d ln J / d theta
@@ -1103,8 +1159,10 @@ extern "C" int fpt_mlp_grad(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t see
         }
         c->scratch_cap = slice;
     }
+    RecordPool rec{};
+    const bool record = record_pool(c, n_traj, s, rec);
     return mlp_grad_run(c, n_traj, dN, seed, traj_offset, tail_lo, objective, s, d_grad, d_G, J_out, n_tail_out,
-                        static_cast<unsigned char *>(c->d_scratch), c->scratch_cap);
+                        static_cast<unsigned char *>(c->d_scratch), c->scratch_cap, record ? &rec : nullptr);
 }
 
 // ---------------------------------------------------------------------------

@@ -519,11 +519,16 @@ __device__ __forceinline__ float grid_amp32(const GridConsts32 &g, const float4 
     return fmaf(f1, b1 - b0, b0);
 }
 
-// Where a replay sends its results.
+// How the lanes of a kernel gather gradient factors: not at all, replaying listed paths whose weight is
+// known, or recording each path's sums per visited cell while it is sampled (weighted afterwards).
+enum : int { kGradNone = 0, kGradReplay = 1, kGradRecord = 2 };
+
+// Where a replay or a recording run sends its results.
 struct ReplayTo {
     const TailEntry *tail;
     double *l_G;                       // node weights of the block (LDS), n0 n1
     unsigned long long *mismatch;      // global count of replays that did not end with a passage
+    RecordPool rec;                    // recording run
 };
 
 // Add a lane's running sums for `cell` (corner order (i0, i1), (i0 + 1, i1),
@@ -538,6 +543,26 @@ __device__ __forceinline__ void grad_flush(const ReplayTo &rp, int n1c, int cell
         atomicAdd(&rp.l_G[k + n1], ww * (double)s[1]);
         atomicAdd(&rp.l_G[k + 1], ww * (double)s[2]);
         atomicAdd(&rp.l_G[k + n1 + 1], ww * (double)s[3]);
+    }
+    s[0] = s[1] = s[2] = s[3] = T(0);
+}
+
+// Append a lane's running sums for `cell` to the records of trajectory rel; k counts the path's records,
+// also those beyond the pool's room (the path is then replayed).
+template <typename T>
+__device__ __forceinline__ void grad_record(const RecordPool &p, uint64_t rel, uint32_t &k, int cell, T s[4])
+{
+    if (cell >= 0) {
+        if (k < p.cap) {
+            const uint64_t at = rel * p.cap + k;
+            T *q = static_cast<T *>(p.sums) + 4 * at;
+            q[0] = s[0];
+            q[1] = s[1];
+            q[2] = s[2];
+            q[3] = s[3];
+            p.cell[at] = (uint16_t)cell;
+        }
+        ++k;
     }
     s[0] = s[1] = s[2] = s[3] = T(0);
 }
@@ -766,12 +791,12 @@ __device__ __forceinline__ bool feed_goes_on(const Feed &f, uint32_t turn)
 // ---------------------------------------------------------------------------
 // TAB: 0 a single node (constant noise); 1 nodes in phi; 2 nodes in the run's time n dN (the
 // table's phi_lo and inv_h then refer to N).
-template <int BIAS, int TAB, bool ALLPOS, bool GRAD, int POT = kPotPiecewiseLinear, bool FEED = false>
+template <int BIAS, int TAB, bool ALLPOS, int GRAD, int POT = kPotPiecewiseLinear, bool FEED = false>
 __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, const double2 *l_tab, const double2 *l_grid,
                                            const RetireTo &rt, const ReplayTo &rp, unsigned long long *cursor,
                                            uint64_t n_traj, uint64_t traj_offset, const Feed &feed = Feed{})
 {
-    static_assert(!GRAD || BIAS == kBiasMlp, "replay needs the tabulated control");
+    static_assert(!GRAD || BIAS == kBiasMlp, "gradients need the tabulated control");
     constexpr bool LEARNED = BIAS == kBiasMlp || BIAS == kBiasMlpExact;
     const double *l_w = reinterpret_cast<const double *>(l_grid);
     const uint32_t every = (uint32_t)I.mlp_every;
@@ -797,16 +822,17 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     uint32_t n = 0;
     double a_held = 0.0;      // exact network: its output at the last evaluation
     uint32_t next_eval = 0;   // exact network: the step of the next evaluation
-    uint64_t traj = 0;        // GRAD: the listed trajectory
-    double ww = 0.0;          // GRAD: its weight w^2
+    uint64_t traj = 0;        // replay: the listed trajectory
+    double ww = 0.0;          // replay: its weight w^2
     int g_cell = -1;          // GRAD: cell of the running sums
+    uint32_t g_k = 0;         // recording: the path's records so far
     double g_s[4] = {0.0, 0.0, 0.0, 0.0};
-    if (GRAD && has) {
+    if (GRAD == kGradReplay && has) {
         traj = rp.tail[rel].traj;
         ww = rp.tail[rel].ww;
     }
     PhiloxPre pre{};
-    if (!FEED) pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+    if (!FEED) pre = philox_pre(GRAD == kGradReplay ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
 
     // Groups below the kink: a live lane has |pi| < sqrt 2 (the start aside) and |xi| < 6.8 (the Box-Muller
     // radius is at most sqrt(66 ln 2)), so in four steps it moves less than `reach`; where every live lane
@@ -910,7 +936,8 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             }
             if (GRAD && live) {
                 if (cell != g_cell) {
-                    grad_flush(rp, gc.n1c, g_cell, g_s, ww);
+                    if (GRAD == kGradReplay) grad_flush(rp, gc.n1c, g_cell, g_s, ww);
+                    else grad_record(rp.rec, rel, g_k, g_cell, g_s);
                     g_cell = cell;
                 }
                 grad_add(g_s, (ALLPOS || S > 0.0) ? -zs : 0.0, f0, f1);
@@ -945,7 +972,13 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             }
         }
         if (fresh) {
-            if (GRAD) {
+            if (GRAD == kGradRecord) {
+                grad_record(rp.rec, rel, g_k, g_cell, g_s);
+                rp.rec.count[rel] = g_k;
+                g_cell = -1;
+                g_k = 0;
+            }
+            if (GRAD == kGradReplay) {
                 grad_flush(rp, gc.n1c, g_cell, g_s, ww);
                 g_cell = -1;
                 if (ev_status != 0u) atomicAdd(rp.mismatch, 1ull);
@@ -1015,11 +1048,11 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             n = 0;
             a_held = 0.0;
             next_eval = 0;
-            if (GRAD) {
+            if (GRAD == kGradReplay) {
                 traj = rp.tail[rel].traj;
                 ww = rp.tail[rel].ww;
             }
-            pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+            pre = philox_pre(GRAD == kGradReplay ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
         }
     }
 }
@@ -1110,12 +1143,12 @@ __device__ __forceinline__ void box_muller32(uint32_t wa, uint32_t wb, float m2l
     zb = fmaf(rho, __builtin_amdgcn_sinf(ub), off);
 }
 
-template <int BIAS, int TAB, bool ALLPOS, bool GRAD, bool FEED = false>
+template <int BIAS, int TAB, bool ALLPOS, int GRAD, bool FEED = false>
 __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, const float4 *l_tab, const float4 *l_grid,
                                            const RetireTo &rt, const ReplayTo &rp, unsigned long long *cursor,
                                            uint64_t n_traj, uint64_t traj_offset, const Feed &feed = Feed{})
 {
-    static_assert(!GRAD || BIAS == kBiasMlp, "replay needs the tabulated control");
+    static_assert(!GRAD || BIAS == kBiasMlp, "gradients need the tabulated control");
     constexpr bool LEARNED = BIAS == kBiasMlp || BIAS == kBiasMlpExact;
     // steps per group: 16 (four generator calls), so that the group's fixed work (table record,
     // renormalisation, FP64 sums, loop control) is shared by 16 steps; the normals of the whole
@@ -1150,16 +1183,17 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
     uint32_t n = 0;
     float a_held = 0.0f;      // exact network: its output at the last evaluation
     uint32_t next_eval = 0;   // exact network: the step of the next evaluation
-    uint64_t traj = 0;        // GRAD: the listed trajectory
-    double ww = 0.0;          // GRAD: its weight w^2
+    uint64_t traj = 0;        // replay: the listed trajectory
+    double ww = 0.0;          // replay: its weight w^2
     int g_cell = -1;          // GRAD: cell of the running sums
+    uint32_t g_k = 0;         // recording: the path's records so far
     float g_s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (GRAD && has) {
+    if (GRAD == kGradReplay && has) {
         traj = rp.tail[rel].traj;
         ww = rp.tail[rel].ww;
     }
     PhiloxPre pre{};
-    if (!FEED) pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+    if (!FEED) pre = philox_pre(GRAD == kGradReplay ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
 
     // constant bias: each step's normal carries the drift shift, z = xi sqrt(dN) + c.adN with
     // c.adN = fl32(A dN), so the exponent of eq. (weight_A) in 1D over k steps,
@@ -1339,7 +1373,8 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             }
             if (GRAD && live) {
                 if (cell != g_cell) {
-                    grad_flush(rp, gc.n1c, g_cell, g_s, ww);
+                    if (GRAD == kGradReplay) grad_flush(rp, gc.n1c, g_cell, g_s, ww);
+                    else grad_record(rp.rec, rel, g_k, g_cell, g_s);
                     g_cell = cell;
                 }
                 grad_add(g_s, (ALLPOS || S > 0.0f) ? -zj : 0.0f, f0, f1);
@@ -1385,7 +1420,13 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         if (LEARNED) lnw -= (double)zacc;
         else zsum += (double)zacc;
         if (fresh) {
-            if (GRAD) {
+            if (GRAD == kGradRecord) {
+                grad_record(rp.rec, rel, g_k, g_cell, g_s);
+                rp.rec.count[rel] = g_k;
+                g_cell = -1;
+                g_k = 0;
+            }
+            if (GRAD == kGradReplay) {
                 grad_flush(rp, gc.n1c, g_cell, g_s, ww);
                 g_cell = -1;
                 if ((ev_code & ~kStepMask) != 0u) atomicAdd(rp.mismatch, 1ull);
@@ -1500,11 +1541,11 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             n = 0;
             a_held = 0.0f;
             next_eval = 0;
-            if (GRAD) {
+            if (GRAD == kGradReplay) {
                 traj = rp.tail[rel].traj;
                 ww = rp.tail[rel].ww;
             }
-            pre = philox_pre(GRAD ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
+            pre = philox_pre(GRAD == kGradReplay ? traj : traj_offset + rel, I.instance, R.key0, R.key1);
         }
     }
 }
@@ -1963,11 +2004,11 @@ em_kernel(EmParams p)
     const RetireTo rt = retire_to(p, acc);
     const ReplayTo rp{nullptr, nullptr, nullptr};
     if (PREC == 0)
-        lanes_fp64<BIAS, TAB, ALLPOS, false, POT>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
+        lanes_fp64<BIAS, TAB, ALLPOS, kGradNone, POT>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
                                                   reinterpret_cast<const double2 *>(l_grid), rt, rp, p.cursor,
                                                   p.n_traj, p.traj_offset);
     else
-        lanes_fp32<BIAS, TAB, ALLPOS, false>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab),
+        lanes_fp32<BIAS, TAB, ALLPOS, kGradNone>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab),
                                              reinterpret_cast<const float4 *>(l_grid), rt, rp, p.cursor, p.n_traj,
                                              p.traj_offset);
     __syncthreads();
@@ -1995,10 +2036,10 @@ __device__ __forceinline__ void pair_block(const Inst &I, const RunArgs &R, unsi
     const Feed feed{l_feed + (size_t)pair * kFeedBytes, flags, pair, pairs, first + (uint64_t)pair * 64};
     if (wave < pairs) {
         if (PREC == 0)
-            lanes_fp64<BIAS, TAB, ALLPOS, false, POT, true>(I, R, reinterpret_cast<const double2 *>(l_tab), nullptr,
+            lanes_fp64<BIAS, TAB, ALLPOS, kGradNone, POT, true>(I, R, reinterpret_cast<const double2 *>(l_tab), nullptr,
                                                             rt, rp, nullptr, n_traj, traj_offset, feed);
         else
-            lanes_fp32<BIAS, TAB, ALLPOS, false, true>(I, R, reinterpret_cast<const float4 *>(l_tab), nullptr, rt, rp,
+            lanes_fp32<BIAS, TAB, ALLPOS, kGradNone, true>(I, R, reinterpret_cast<const float4 *>(l_tab), nullptr, rt, rp,
                                                        nullptr, n_traj, traj_offset, feed);
     } else {
         if (PREC == 0)
@@ -2066,6 +2107,8 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY replay_kernel(ReplayPar
     unsigned char *l_grid = l_tab + tab_bytes(PREC, I.n_tab);
     double *l_G = reinterpret_cast<double *>(l_grid + cell_bytes(PREC, grid_cells(I)));
     const int n_nodes = I.g_n0 * I.g_n1;
+    const uint64_t n_tail = *p.n_tail;
+    if (n_tail == 0) return;
     for (int i = threadIdx.x; i < n_nodes; i += blockDim.x) l_G[i] = 0.0;
     if (PREC == 0) stage_table64(I, reinterpret_cast<double2 *>(l_tab));
     else stage_table32(I, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
@@ -2073,23 +2116,94 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY replay_kernel(ReplayPar
     __syncthreads();
     RetireTo rt{};
     const ReplayTo rp{p.tail, l_G, p.mismatch};
-    const uint64_t n_tail = *p.n_tail;
     // The list's length is known on the device alone, so the grid is a full one; where the list does not
     // fill it, each block's first ceil(waves/blocks) waves share it (as run_shape does for fpt_run).
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x) / 64;
     if (wave >= ((n_tail + 63) / 64 + gridDim.x - 1) / gridDim.x) {
         // nothing to replay here
     } else if (PREC == 0)
-        lanes_fp64<kBiasMlp, true, ALLPOS, true>(I, p.run, reinterpret_cast<const double2 *>(l_tab),
+        lanes_fp64<kBiasMlp, 1, ALLPOS, kGradReplay>(I, p.run, reinterpret_cast<const double2 *>(l_tab),
                                                  reinterpret_cast<const double2 *>(l_grid), rt, rp, p.cursor, n_tail,
                                                  0);
     else
-        lanes_fp32<kBiasMlp, true, ALLPOS, true>(I, p.run, reinterpret_cast<const float4 *>(l_tab),
+        lanes_fp32<kBiasMlp, 1, ALLPOS, kGradReplay>(I, p.run, reinterpret_cast<const float4 *>(l_tab),
                                                  reinterpret_cast<const float4 *>(l_grid), rt, rp, p.cursor, n_tail,
                                                  0);
     __syncthreads();
     for (int i = threadIdx.x; i < n_nodes; i += blockDim.x)
         if (l_G[i] != 0.0) unsafeAtomicAdd(&p.d_G[i], l_G[i]);
+}
+
+// Recording run: em_kernel's tabulated control, with each path's gradient sums per visited cell kept.
+template <int PREC, int TAB, bool ALLPOS>
+__global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em_record_kernel(EmParams p, RecordPool rec)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const LdsAcc acc = lds_acc(smem, p.inst.hist.n_bins);
+    unsigned char *l_tab = smem + align16(acc_bytes(p.inst.hist.n_bins));
+    unsigned char *l_grid = l_tab + tab_bytes(PREC, p.inst.n_tab);
+    zero_lds_acc(acc);
+    if (PREC == 0) stage_table64(p.inst, reinterpret_cast<double2 *>(l_tab));
+    else stage_table32(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
+    stage_grid<PREC>(p.inst, l_grid);
+    __syncthreads();
+    const RetireTo rt = retire_to(p, acc);
+    const ReplayTo rp{nullptr, nullptr, nullptr, rec};
+    if (PREC == 0)
+        lanes_fp64<kBiasMlp, TAB, ALLPOS, kGradRecord>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
+                                                       reinterpret_cast<const double2 *>(l_grid), rt, rp, p.cursor,
+                                                       p.n_traj, p.traj_offset);
+    else
+        lanes_fp32<kBiasMlp, TAB, ALLPOS, kGradRecord>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab),
+                                                       reinterpret_cast<const float4 *>(l_grid), rt, rp, p.cursor,
+                                                       p.n_traj, p.traj_offset);
+    __syncthreads();
+    flush_lds_acc(acc, p.inst.acc);
+}
+
+// After a recording run: every path of the tail T (crossed with deltaN >= tail_lo) adds w^2 times its
+// recorded sums to the node weights G, and w^2 and 1 to J_sum and n_tail_total; a path with more records
+// than the pool has room for goes on the replay list instead.  A wave takes one path at a time, a lane
+// one record; node weights are summed in LDS first.
+template <typename T>
+__global__ void __launch_bounds__(1024) tail_weigh_kernel(const double *d_N, const double *d_lnw, const uint32_t *d_steps,
+                                                          uint64_t n, uint64_t traj_offset, double N_ref,
+                                                          double tail_lo, RecordPool rec, int n0, int n1, double *d_G,
+                                                          TailEntry *tail, unsigned long long *n_tail,
+                                                          unsigned long long *n_tail_total, double *J_sum)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *l_G = reinterpret_cast<double *>(smem);
+    for (int i = threadIdx.x; i < n0 * n1; i += blockDim.x) l_G[i] = 0.0;
+    __syncthreads();
+    const ReplayTo rp{nullptr, l_G, nullptr};
+    const int lane = (int)__lane_id(), waves = (int)(gridDim.x * (blockDim.x / 64));
+    double j_sum = 0.0;
+    unsigned long long count = 0;
+    for (uint64_t i = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64; i < n; i += waves) {
+        if ((d_steps[i] & (kFlagCensored | kFlagEndedEarly)) != 0u || !(d_N[i] - N_ref >= tail_lo)) continue;
+        const double ww = exp(2.0 * d_lnw[i]);
+        j_sum += ww;
+        ++count;
+        const uint32_t k = rec.count[i];
+        if (k > rec.cap) {
+            if (lane == 0) tail[atomicAdd(n_tail, 1ull)] = TailEntry{traj_offset + i, ww};
+            continue;
+        }
+        for (uint32_t r = lane; r < k; r += 64) {
+            const uint64_t at = i * rec.cap + r;
+            const T *q = static_cast<const T *>(rec.sums) + 4 * at;
+            T v[4] = {q[0], q[1], q[2], q[3]};
+            grad_flush(rp, n1 - 1, (int)rec.cell[at], v, ww);
+        }
+    }
+    if (lane == 0 && count != 0) {
+        unsafeAtomicAdd(J_sum, j_sum);
+        atomicAdd(n_tail_total, count);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n0 * n1; i += blockDim.x)
+        if (l_G[i] != 0.0) unsafeAtomicAdd(&d_G[i], l_G[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2162,10 +2276,10 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY batch_kernel(const Inst
         rt.hist = I.hist;
         const ReplayTo rp{nullptr, nullptr, nullptr};
         if (PREC == 0)
-            lanes_fp64<BIAS, true, ALLPOS, false>(I, R, reinterpret_cast<const double2 *>(l_tab), nullptr, rt, rp,
+            lanes_fp64<BIAS, 1, ALLPOS, kGradNone>(I, R, reinterpret_cast<const double2 *>(l_tab), nullptr, rt, rp,
                                                   &cursors[1 + W.inst], W.count, W.begin);
         else
-            lanes_fp32<BIAS, true, ALLPOS, false>(I, R, reinterpret_cast<const float4 *>(l_tab), nullptr, rt, rp,
+            lanes_fp32<BIAS, 1, ALLPOS, kGradNone>(I, R, reinterpret_cast<const float4 *>(l_tab), nullptr, rt, rp,
                                                   &cursors[1 + W.inst], W.count, W.begin);
         __syncthreads();
         flush_lds_acc(acc, I.acc);
@@ -2320,6 +2434,49 @@ hipError_t replay_launch(const ReplayParams &p, int precision, int grid, int blo
     ReplayParams pp = p;
     void *args[] = {&pp};
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, stream);
+}
+
+template <int PREC>
+const void *rptr(int tab_mode, bool all_pos)
+{
+    static const void *const t[2][2] = {{reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, false>),
+                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, true>)},
+                                        {reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, false>),
+                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, true>)}};
+    return t[tab_mode ? 1 : 0][all_pos ? 1 : 0];
+}
+
+const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos)
+{
+    return precision == 0 ? rptr<0>(tab_mode, all_pos) : rptr<1>(tab_mode, all_pos);
+}
+
+hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block,
+                            hipStream_t stream)
+{
+    EmParams pp = p;
+    RecordPool rr = rec;
+    void *args[] = {&pp, &rr};
+    return hipLaunchKernel(em_record_kernel_ptr(precision, tab_mode(p.inst), p.inst.all_S_pos != 0), dim3(grid),
+                           dim3(block), args,
+                           em_lds_bytes(p.inst.hist.n_bins, p.inst.n_tab, precision, grid_cells(p.inst)), stream);
+}
+
+hipError_t tail_weigh(const double *d_N, const double *d_lnw, const uint32_t *d_steps, uint64_t n,
+                      uint64_t traj_offset, double N_ref, double tail_lo, const RecordPool &rec, int precision, int n0,
+                      int n1, double *d_G, TailEntry *tail, unsigned long long *n_tail,
+                      unsigned long long *n_tail_total, double *J_sum, int cu_count, hipStream_t stream)
+{
+    const uint64_t most = (n + 15) / 16;
+    const dim3 grid((unsigned)(most < (uint64_t)cu_count ? most : (uint64_t)cu_count)), block(1024);
+    const size_t lds = (size_t)n0 * n1 * sizeof(double);
+    if (precision == 0)
+        hipLaunchKernelGGL(tail_weigh_kernel<double>, grid, block, lds, stream, d_N, d_lnw, d_steps, n, traj_offset,
+                           N_ref, tail_lo, rec, n0, n1, d_G, tail, n_tail, n_tail_total, J_sum);
+    else
+        hipLaunchKernelGGL(tail_weigh_kernel<float>, grid, block, lds, stream, d_N, d_lnw, d_steps, n, traj_offset,
+                           N_ref, tail_lo, rec, n0, n1, d_G, tail, n_tail, n_tail_total, J_sum);
+    return hipGetLastError();
 }
 
 const void *batch_kernel_ptr(int precision, int bias_kind, bool all_pos)

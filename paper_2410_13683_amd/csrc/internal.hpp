@@ -134,6 +134,16 @@ struct TailEntry {
     double ww;                       // w_old w_theta of the path (w^2 on-policy)
 };
 
+// Gradient sums per visited grid cell, recorded while a slice of trajectories is sampled: record k < cap of
+// trajectory i is sums[4 (i cap + k) ..] (FP64 or FP32, the run's precision) for cell[i cap + k];
+// count[i] records were made, also beyond cap.
+struct RecordPool {
+    void *sums;
+    uint16_t *cell;
+    uint32_t *count;
+    uint32_t cap;
+};
+
 // One launch of the replay kernel: the trajectories of `tail`, integrated again
 // with the instance's tabulated control, scatter their per-step gradient factors
 // onto the grid nodes `d_G` (n0 n1 doubles, accumulated with atomics).
@@ -169,6 +179,14 @@ size_t em2d_lds_bytes(int n_bins, int n_tab, int precision);
 const void *em2d_kernel_ptr(int precision, int bias_kind, bool all_pos, bool time_axis);
 hipError_t em2d_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream);
 hipError_t replay_launch(const ReplayParams &p, int precision, int grid, int block, hipStream_t stream);
+// Recording runs (the tabulated control; tab_mode 0 or 1) and the weighting of their tail (see fpt_em.hip).
+const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos);
+hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block,
+                            hipStream_t stream);
+hipError_t tail_weigh(const double *d_N, const double *d_lnw, const uint32_t *d_steps, uint64_t n,
+                      uint64_t traj_offset, double N_ref, double tail_lo, const RecordPool &rec, int precision, int n0,
+                      int n1, double *d_G, TailEntry *tail, unsigned long long *n_tail,
+                      unsigned long long *n_tail_total, double *J_sum, int cu_count, hipStream_t stream);
 const void *batch_kernel_ptr(int precision, int bias_kind, bool all_pos);
 // cursors: [0] the ticket cursor, [1 + i] instance i's trajectory cursor (zeroed before each launch)
 hipError_t batch_launch(int precision, int bias_kind, bool all_pos, const Inst *insts, const WorkItem *items,
