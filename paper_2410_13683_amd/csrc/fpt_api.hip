@@ -755,8 +755,8 @@ static int occupancy_grid(const void *fn, int block, size_t lds, int cu_count, i
 // SIMDs in turn), since up to a trajectory per lane the time is that of one trajectory beside its
 // SIMD's other waves.  On full blocks the first ones to reach the cursor filled all their 16 waves
 // while other CUs stood idle: 1e5 FP32 trajectories (slow roll -> ultra-slow roll) took 12 to 18 ms from
-// launch to launch and take 11.9; 65,536 FP64 ones 44.1 -> 24.3 ms, 131,072 56.6 -> 32.8 ms; 1e4 of the
-// linear problem 1.57 -> 1.42 ms.  From one wave on every slot of the full grid (262,144 trajectories)
+// launch to launch and took 11.9; 65,536 FP64 ones 44.1 -> 24.3 ms, 131,072 56.6 -> 32.8 ms; 1e4 of the
+// linear problem 1.57 -> 1.42 ms (all before paired waves, which most runs of these sizes take now).  From one wave on every slot of the full grid (262,144 trajectories)
 // the shapes are the same.
 static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_traj, int &grid, int &block,
                      int block_max = 1024)
@@ -811,11 +811,11 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     const int rc = run_shape(c, fn, lds, n_traj, grid, block, exact && c->precision == FPT_FP32_STATE ? kMaxBlockNet32 : 1024);
     if (rc) return rc;
     // Paired waves (em_pair_kernel) up to 64 kFeedMaxPairs trajectories per CU, i.e. two integrating waves per
-    // SIMD, whose partners fill its other two: 65,536 trajectories (slow roll -> ultra-slow roll) take 8.5
-    // against 9.6 ms unpaired in FP32 state and 18.9 against 24.3 ms in FP64, 131,072 take 10.8 against 11.8
-    // and 29.5 against 32.8 ms, 1e4 of the linear problem 1.08 against 1.42 ms; beyond, four integrating waves
-    // per SIMD keep it busy by themselves.  Odd counts above 4 are rounded up: 7 pairs took 12.1 ms where 8
-    // take 10.7.
+    // SIMD, whose partners fill its other two: 65,536 trajectories (slow roll -> ultra-slow roll) take 7.1
+    // against 9.7 ms unpaired in FP32 state (10.8 against 16.6 on the e-fold axis) and 17.3 against 22.2 ms in
+    // FP64, 131,072 take 10.0 against 11.8 and 28.1 against 30.2 ms, 1e4 of the linear problem 0.81 against
+    // 1.30 ms; beyond, four integrating waves per SIMD keep it busy by themselves.  Odd counts above 4 are
+    // rounded up: seven pairs took longer than eight (12.1 against 10.7 ms).
     const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
     uint64_t pairs = (waves + cus - 1) / cus;
     if (pairs > 4) pairs += pairs & 1;
@@ -1508,7 +1508,7 @@ static int batch_launch_items(fpt_batch *b, const std::vector<WorkItem> &items, 
 // which every block has one slice of one instance and there is at most one block per CU; 0 where eight
 // do not suffice or do not fit in LDS.  In the general kernel an instance's trajectories go to whichever
 // 16-wave blocks get to them, most of whose waves stay idle then: 64 instances of 100 to 1000
-// trajectories (2^16 steps) took 11.9 ms and take 5.0, of 500 to 5000 12.2 and 6.7 ms.
+// trajectories (2^16 steps) took 11.8 ms and take 3.3, of 500 to 5000 12.4 and 6.7 ms.
 static int batch_pairs(const fpt_batch *b, const uint64_t *n_traj)
 {
     if (b->fixed_block) return 0;

@@ -219,6 +219,13 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// x^2/2 rounded by itself (never part of a fused multiply-add).
+__device__ __forceinline__ double half_sq(double x)
+{
+#pragma clang fp contract(off)
+    return 0.5 * x * x;
+}
+
 // Steps left before max_steps for the wave's most advanced lane that holds a trajectory, as a
 // wave-uniform value (such a lane has at most max_steps steps: a lane reaching it is censored).
 // At the start of a chunk it bounds every lane's count inside the chunk (all lanes step
@@ -855,17 +862,24 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     const double quiet_N = I.phi_lo + (double)I.n_tab / I.inv_h;
     auto quiet_lane = [&]() -> bool { return TAB == 1 ? phi < I.phi_lo : (double)n * dN > quiet_N; };
 
-    // Returns false only for a QUIET group that left the quiet region (nothing is recorded then).
-    auto group = [&](auto censor_tag, auto below_tag, auto quiet_tag, const double z[4]) -> bool {
+    // Returns false for a QUIET group that left the quiet region, and for a group without EVENTS in which a
+    // live lane's path ended: nothing is recorded then, and the state is the group's start again.  Paired
+    // waves step without EVENTS first: one wave on its SIMD waits out the event's branch in every step, and
+    // a wave's 64 paths end in at most 64 of its 2.5e4 groups (16,384 trajectories, slow roll -> ultra-slow
+    // roll: 15.9 -> 14.4 ms here, 7.6 -> 5.0 in lanes_fp32; with more waves per SIMD they hide that wait, and
+    // the shorter code of one variant runs no slower).
+    auto group = [&](auto censor_tag, auto below_tag, auto quiet_tag, auto events_tag, const double z[4]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool BELOW = decltype(below_tag)::value;
         constexpr bool QUIET = decltype(quiet_tag)::value;
+        constexpr bool EVENTS = decltype(events_tag)::value;
         bool fresh = false;
         uint32_t ev_status, ev_n;   // written before use: read only where fresh is set
         double ev_N, ev_lnw;
         const bool live0 = live;
-        const double phi0 = phi, pi0 = pi_;
-        bool left_quiet = false;
+        const double phi0 = phi, pi0 = pi_, lnw0 = lnw;
+        bool left_quiet = false, any_end = false;
+        double eps1 = 0.0;          // pi^2/2 after the last step
 #pragma unroll(BIAS == kBiasMlpExact ? 1 : 4)   // the exact network: one copy of its code
         for (int j = 0; j < 4; ++j) {
             if (CENSOR && live && n == I.max_steps) {
@@ -900,6 +914,9 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
                 S = S0;
                 t = t0;
             }
+            // 3 - pi^2/2: one fused operation in the group's first step, from the end test's rounded pi^2/2 in
+            // the others.  Written out, so that every variant of the group rounds alike.
+            const double q_pi = (j == 0 || BIAS == kBiasMlpExact) ? fma(-pi_, 0.5 * pi_, 3.0) : 3.0 - eps1;
             double a = a_const;
             int cell = 0;
             double f0 = 0.0, f1 = 0.0;
@@ -919,7 +936,7 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             const double aS = a * S;
             const double phi_n = QUIET ? phi + pi_ * dN
                                  : (BIAS == kBiasNone) ? phi + pi_ * dN + noise : phi + (pi_ + aS) * dN + noise;
-            const double drift_pi = pi_ - (3.0 - 0.5 * pi_ * pi_) * (pi_ + r) * dN;
+            const double drift_pi = pi_ - q_pi * (pi_ + r) * dN;
             const double pi_n = QUIET ? drift_pi
                                 : (BIAS == kBiasNone) ? drift_pi + t * noise : drift_pi + t * (aS * dN + noise);
             if (QUIET) {
@@ -945,7 +962,10 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             // live and fresh are updated outside the branch, so that they stay lane masks; the event's inputs
             // pass through an empty volatile asm, which keeps its work (a second comparison with phi_end, a
             // division) from moving in front of the branch, into every step
-            const bool hit = live & ((phi_n <= phi_end) | (0.5 * pi_n * pi_n >= 1.0));
+            eps1 = half_sq(pi_n);
+            const bool ends = (phi_n <= phi_end) | (eps1 >= 1.0);
+            const bool hit = EVENTS && (live & ends);
+            if (!EVENTS) any_end = any_end | ends;
             if (hit) {
                 double pa = phi, pb = phi_n;
                 uint32_t nb = n;
@@ -962,10 +982,11 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
             pi_ = pi_n;
             n += 1;
         }
-        if (QUIET && TAB == 1) {
-            if (__builtin_amdgcn_ballot_w64(live0 && left_quiet) != 0) {
+        if ((QUIET && TAB == 1) || !EVENTS) {
+            if (__builtin_amdgcn_ballot_w64(live0 && (left_quiet || any_end)) != 0) {
                 phi = phi0;
                 pi_ = pi0;
+                lnw = lnw0;
                 live = live0;
                 n -= 4;
                 return false;
@@ -992,15 +1013,18 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     using No = std::integral_constant<bool, false>;
     // The group's variant from its normals; `may_cap`: a lane may reach max_steps in it.
     auto noisy_group = [&](bool may_cap, const double z[4]) {
-        if (may_cap) group(Yes(), No(), No(), z);
-        else if (CAN_BELOW && all_below()) group(No(), std::integral_constant<bool, CAN_BELOW>(), No(), z);
-        else group(No(), No(), No(), z);
+        using Below = std::integral_constant<bool, CAN_BELOW>;
+        using Last = std::integral_constant<bool, !FEED>;      // paired waves: without events first
+        if (may_cap) group(Yes(), No(), No(), Yes(), z);
+        else if (CAN_BELOW && all_below()) {
+            if (!group(No(), Below(), No(), Last(), z)) group(No(), Below(), No(), Yes(), z);
+        } else if (!group(No(), No(), No(), Last(), z)) group(No(), No(), No(), Yes(), z);
     };
     auto quiet_group = [&](bool may_cap) -> bool {
         if constexpr (CAN_QUIET) {
             const double none[4] = {0.0, 0.0, 0.0, 0.0};
             if (may_cap || !quiet_table || __builtin_amdgcn_ballot_w64(live && !quiet_lane()) != 0) return false;
-            return group(No(), No(), Yes(), none);
+            return group(No(), No(), Yes(), Yes(), none);
         }
         return false;
     };
@@ -1262,10 +1286,16 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
                (xh - c.xT_hi) + (xl - c.xT_lo) < below && fabsf(ps) <= pi_plain;
     };
 
-    auto group = [&](auto censor_tag, auto span_tag, auto end_tag, const float z[G]) {
+    // As in lanes_fp64, a group without EVENTS returns false, at the group's start again, if a live lane's
+    // path ends in it.
+    auto group = [&](auto censor_tag, auto span_tag, auto end_tag, auto events_tag, const float z[G]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool SPAN = decltype(span_tag)::value;
         constexpr bool END = decltype(end_tag)::value;   // test the eps_1 = 1 end in each step
+        constexpr bool EVENTS = decltype(events_tag)::value;
+        const float xl0 = xl, pl0 = pl, xs0 = xs, ps0 = ps;
+        const uint32_t n_on0 = n_on;
+        bool any_end = false;
         static_assert(!SPAN || (TAB != 0 && !CENSOR), "one record per group, or a plain time group: no censoring");
         // a SPAN group of a time table is plain: below the kink, inside the table, S > 0 (plain_lane)
         constexpr bool PLAIN = TAB == 2 && SPAN;
@@ -1396,7 +1426,8 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             // live lane can get there (pi_safe above)
             const bool ended = END && fabsf(ps) >= 0x1.6a09e8p+0f;
             // live and fresh are updated outside the branch, so that they stay lane masks
-            const bool hit = live && (crossed || ended);
+            const bool hit = EVENTS && live && (crossed || ended);
+            if (!EVENTS) any_end = any_end | crossed | ended;
             if (hit) {
                 // both candidates, then a select on the crossing mask: no divergent branch inside.
                 // The state passes through an empty volatile asm first, which keeps the compiler
@@ -1414,6 +1445,16 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             }
             live = live && !hit;
             fresh = fresh || hit;
+        }
+        if (!EVENTS) {
+            if (__builtin_amdgcn_ballot_w64(live && any_end) != 0) {
+                xl = xl0;
+                pl = pl0;
+                xs = xs0;
+                ps = ps0;
+                n_on = n_on0;
+                return false;
+            }
         }
         n += G;
         if (PLAIN && !ALLPOS && BIAS == kBiasConst) n_on += G;
@@ -1441,12 +1482,14 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
         xh = xs;
         pl = pl - (ps - ph);
         ph = ps;
+        return true;
     };
 
     // One group from its normals; `may_cap`: a lane may reach max_steps in it.
     auto run_group = [&](bool may_cap, const float z[G]) {
         using T = std::integral_constant<bool, true>;
         using F = std::integral_constant<bool, false>;
+        using L = std::integral_constant<bool, !FEED>;         // paired waves: without events first
         if constexpr (TAB == 1) {
             // the record of the lane's interval at the group start
             const float u0 = __builtin_amdgcn_fmed3f(fmaf(xs, c.inv_h, c.u_off), 0.0f, c.jtop);
@@ -1462,23 +1505,28 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             g_dr = g_rn.y * c.inv_h;
         }
         if (may_cap) {
-            group(T(), F(), T(), z);
+            group(T(), F(), T(), T(), z);
         } else {
             if constexpr (TAB == 1) {
                 if (__builtin_amdgcn_ballot_w64(live && g_r != g_r) != 0) {
-                    group(F(), F(), T(), z);
+                    group(F(), F(), T(), T(), z);
                 } else if constexpr (LEARNED) {
-                    group(F(), T(), T(), z);
+                    group(F(), T(), T(), T(), z);
                 } else {
-                    if (__builtin_amdgcn_ballot_w64(live && fabsf(ps) > pi_safe) == 0)
-                        group(F(), T(), F(), z);
-                    else group(F(), T(), T(), z);
+                    if (__builtin_amdgcn_ballot_w64(live && fabsf(ps) > pi_safe) == 0) {
+                        if (!group(F(), T(), F(), L(), z)) group(F(), T(), F(), T(), z);
+                    } else {
+                        group(F(), T(), T(), T(), z);
+                    }
                 }
             } else if constexpr (TAB == 2) {
-                if (__builtin_amdgcn_ballot_w64(live && !plain_lane()) == 0) group(F(), T(), F(), z);
-                else group(F(), F(), T(), z);
+                if (__builtin_amdgcn_ballot_w64(live && !plain_lane()) == 0) {
+                    if (!group(F(), T(), F(), L(), z)) group(F(), T(), F(), T(), z);
+                } else {
+                    group(F(), F(), T(), T(), z);
+                }
             } else {
-                group(F(), F(), T(), z);
+                if (!group(F(), F(), T(), L(), z)) group(F(), F(), T(), T(), z);
             }
         }
     };
