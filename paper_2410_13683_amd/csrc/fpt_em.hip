@@ -142,7 +142,7 @@ __device__ __forceinline__ void philox_call(uint32_t m, const PhiloxPre &q, uint
 constexpr int kBmN = 256;
 constexpr size_t kBmBytes = 2 * kBmN * sizeof(double2);
 
-// l_bm[j] = (sin A_j, cos A_j); l_bm[kBmN + i] = (r_i, L_i)
+// l_bm[j] = (sin A_j, cos A_j); l_bm[kBmN + i] = (r_i, -2 L_i)
 __device__ __forceinline__ void stage_bm(double2 *l_bm)
 {
     for (int i = threadIdx.x; i < 2 * kBmN; i += blockDim.x) {
@@ -154,7 +154,7 @@ __device__ __forceinline__ void stage_bm(double2 *l_bm)
             const int k = i - kBmN;
             const double c = (k == kBmN - 1) ? 1.0 : 0.5 * (1.0 + (k + 0.5) * (1.0 / 256.0));
             const double r = 1.0 / c;
-            l_bm[i] = make_double2(r, -log(r));
+            l_bm[i] = make_double2(r, 2.0 * log(r));
         }
     }
 }
@@ -175,20 +175,21 @@ __device__ __forceinline__ double sqrt_mid(double x)
 __device__ __forceinline__ void box_muller64(uint32_t wa, uint32_t wb, double sqrt_dN, const double2 *l_bm,
                                              double &za, double &zb)
 {
-    const double ua = fma((double)wa, 0x1p-32, 0x1p-33);
+    const double ua = (double)wa + 0.5;                      // u 2^32
     const double m = __builtin_amdgcn_frexp_mant(ua);        // [0.5, 1)
-    const int e = __builtin_amdgcn_frexp_exp(ua);
+    const int e = __builtin_amdgcn_frexp_exp(ua) - 32;
     const int i = (__double2hiint(m) >> 12) & 0xff;
     const double2 lt = l_bm[kBmN + i];
     const double t = fma(m, lt.x, -1.0);
-    double q = fma(t, 0.2, -0.25);
-    q = fma(t, q, 1.0 / 3.0);
-    q = fma(t, q, -0.5);
+    double q = fma(t, -0.4, 0.5);
+    q = fma(t, q, -2.0 / 3.0);
     q = fma(t, q, 1.0);
-    const double ln_u = fma((double)e, 0x1.62e42fefa39efp-1, fma(t, q, lt.y));   // e ln 2 + L_i + ln(1 + t)
-    const double rho = sqrt_mid(-2.0 * ln_u) * sqrt_dN;
-    const int d = (int)((wb & 0xffffffu) << 1) + 1 - (1 << 24);
-    const double th = (double)d * 0x1.921fb54442d18p-31;                          // 2 pi d 2^-33
+    q = fma(t, q, -2.0);
+    const double m2ln_u = fma((double)e, -0x1.62e42fefa39efp+0, fma(t, q, lt.y));   // -2 (e ln 2 + L_i + ln(1 + t))
+    const double rho = sqrt_mid(m2ln_u) * sqrt_dN;
+    // 128 d as the signed integer that w's low 24 bits and a half form at the top of a word
+    const int d128 = (int)(((wb << 8) | 0x80u) ^ 0x80000000u);
+    const double th = (double)d128 * 0x1.921fb54442d18p-38;                       // 2 pi d 2^-33
     const double th2 = th * th;
     const double sn = th * fma(th2, fma(th2, 1.0 / 120.0, -1.0 / 6.0), 1.0);
     const double cs = fma(th2, fma(th2, fma(th2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);
