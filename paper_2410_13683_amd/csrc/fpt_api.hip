@@ -810,20 +810,25 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
                                             exact);
     const int rc = run_shape(c, fn, lds, n_traj, grid, block, exact && c->precision == FPT_FP32_STATE ? kMaxBlockNet32 : 1024);
     if (rc) return rc;
-    // Paired waves (em_pair_kernel) up to 64 kFeedMaxPairs trajectories per CU, i.e. two integrating waves per
+    // Paired waves (em_pair_kernel, em2d_pair_kernel) up to 64 kFeedMaxPairs trajectories per CU, i.e. two integrating waves per
     // SIMD, whose partners fill its other two: 65,536 trajectories (slow roll -> ultra-slow roll) take 7.1
     // against 9.7 ms unpaired in FP32 state (10.8 against 16.6 on the e-fold axis) and 17.3 against 22.2 ms in
     // FP64, 131,072 take 10.0 against 11.8 and 28.1 against 30.2 ms, 1e4 of the linear problem 0.81 against
-    // 1.30 ms; beyond, four integrating waves per SIMD keep it busy by themselves.  Odd counts above 4 are
+    // 1.30 ms; with 2D noise 32,768 take 19.6 against 36.9 ms in FP64 and 8.6 against 13.3 in FP32 state,
+    // 65,536 26.5 against 34.4 and 10.9 against 13.2 (beyond, a table of 2048 nodes leaves no LDS for the
+    // buffers of more than five pairs); beyond, four integrating waves per SIMD keep it busy by themselves.  Odd counts above 4 are
     // rounded up: seven pairs took longer than eight (12.1 against 10.7 ms).
     const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
     uint64_t pairs = (waves + cus - 1) / cus;
     if (pairs > 4) pairs += pairs & 1;
-    const size_t pair_lds = lds + pairs * kFeedBytes;
+    const size_t pair_lds = lds + pairs * (two_d ? 2 : 1) * kFeedBytes;
     const void *pair_fn = nullptr;
-    if (!two_d && !c->opt.block_size && !c->opt.blocks_per_cu && pairs <= (uint64_t)kFeedMaxPairs &&
+    if (!c->opt.block_size && !c->opt.blocks_per_cu && pairs <= (uint64_t)kFeedMaxPairs &&
         pair_lds + kFeedFlagBytes <= c->lds_per_block_max)
-        pair_fn = em_pair_kernel_ptr(c->precision, bias_k, tab_mode(c->inst), c->inst.all_S_pos != 0, c->inst.pot_kind);
+        pair_fn = two_d ? em2d_pair_kernel_ptr(c->precision, c->inst.bias_kind, c->inst.all_S_pos != 0,
+                                               tab_mode(c->inst) == 2)
+                        : em_pair_kernel_ptr(c->precision, bias_k, tab_mode(c->inst), c->inst.all_S_pos != 0,
+                                             c->inst.pot_kind);
     if (pair_fn) {
         HIP_TRY(hipEventRecord(c->ev_start, s));
         void *args[] = {&p};

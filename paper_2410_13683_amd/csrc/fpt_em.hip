@@ -138,6 +138,10 @@ __device__ __forceinline__ void philox_call(uint32_t m, const PhiloxPre &q, uint
 //          theta^6 (errors < 1e-17 and < 2e-23), and the angle-addition formulas combine them.
 // Both stay far below what per-trajectory agreement to 1e-9 with an FP64 reference needs
 // (normals to ~1e-9): the series stop where the next term is below 1e-17.
+// VALU issue bounds it, so powers of two are folded where that leaves every bit as it is: the factor -2 of
+// sqrt(-2 ln u) into the table and the series, 2^-32 into the exponent, the angle's integer formed in the
+// top bits of a word (four operations fewer per pair; 1e4 trajectories of the linear problem 0.89 -> 0.86
+// ms, 65,536 of slow roll -> ultra-slow roll 17.3 -> 16.7, 1e6 183.7 -> 182.0).
 // Returns xi sqrt(dN) for the two steps of the pair.
 constexpr int kBmN = 256;
 constexpr size_t kBmBytes = 2 * kBmN * sizeof(double2);
@@ -1083,6 +1087,7 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
 }
 
 // The partner of a paired FP64 wave: the normals of kFeedSteps steps (two or more generator calls) a turn.
+template <int DIM>
 __device__ __forceinline__ void feed_fp64(const Inst &I, const RunArgs &R, const double2 *l_bm, uint64_t traj_offset,
                                           const Feed &feed)
 {
@@ -1091,7 +1096,7 @@ __device__ __forceinline__ void feed_fp64(const Inst &I, const RunArgs &R, const
     uint32_t m = 0;
     for (uint32_t turn = 0;; ++turn) {
 #pragma unroll
-        for (int q = 0; q < kFeedSteps / 2; q += 2) {
+        for (int q = 0; q < DIM * kFeedSteps / 2; q += 2) {
             uint32_t w[4];
             philox_call(m++, pre, R.key0, R.key1, w);
             double2 a, b;
@@ -1599,20 +1604,22 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
     }
 }
 // The partner of a paired FP32 wave: the shifted normals of one group (four generator calls) a turn.
+template <int DIM>
 __device__ __forceinline__ void feed_fp32(const Inst &I, const RunArgs &R, uint64_t traj_offset, const Feed &feed)
 {
     const F32Consts c = f32_consts(I, R);
+    const float shift = DIM == 2 ? 0.0f : c.adN;      // 2D: a constant bias shifts along e, in the step
     const PhiloxPre pre = philox_pre(traj_offset + feed.first + __lane_id(), I.instance, R.key0, R.key1);
     float4 *buf = reinterpret_cast<float4 *>(feed.buf) + __lane_id();
     uint32_t m = 0;
     for (uint32_t turn = 0;; ++turn) {
 #pragma unroll
-        for (int q = 0; q < kFeedSteps32 / 4; ++q) {
+        for (int q = 0; q < DIM * kFeedSteps32 / 4; ++q) {
             uint32_t w[4];
             philox_call(m++, pre, R.key0, R.key1, w);
             float4 v;
-            box_muller32(w[0], w[1], c.m2ln2_dN, c.adN, v.x, v.y);
-            box_muller32(w[2], w[3], c.m2ln2_dN, c.adN, v.z, v.w);
+            box_muller32(w[0], w[1], c.m2ln2_dN, shift, v.x, v.y);
+            box_muller32(w[2], w[3], c.m2ln2_dN, shift, v.z, v.w);
             buf[64 * q] = v;
         }
         __syncthreads();
@@ -1646,10 +1653,10 @@ __device__ __forceinline__ Node2d lerp_node2d(const double2 *l_tab, int j, doubl
     return n;
 }
 
-template <int BIAS, bool ALLPOS, bool TIME>
+template <int BIAS, bool ALLPOS, bool TIME, bool FEED = false>
 __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, const double2 *l_tab,
                                               const RetireTo &rt, unsigned long long *cursor, uint64_t n_traj,
-                                              uint64_t traj_offset)
+                                              uint64_t traj_offset, const Feed &feed = Feed{})
 {
     const DriftConsts dk = drift_consts(I);
     const double dN = R.dN, sqrt_dN = R.sqrt_dN, phi_end = I.phi_end, phi_T = I.phi_T;
@@ -1660,12 +1667,13 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
     const double s_plus = in_vgpr(dk.s_plus), s_minus = in_vgpr(dk.s_minus);
 
     bool exhausted = false;
-    uint64_t rel = 0;
-    bool has = claim(true, rel, cursor, n_traj, exhausted);
+    uint64_t rel = FEED ? feed.first + __lane_id() : 0;
+    bool has = FEED ? rel < n_traj : claim(true, rel, cursor, n_traj, exhausted);
     bool live = has;
     double phi = I.phi_in, pi_ = I.pi_in, lnw = 0.0;
     uint32_t n = 0;
-    PhiloxPre pre = philox_pre(traj_offset + rel, I.instance, R.key0, R.key1);
+    PhiloxPre pre{};
+    if (!FEED) pre = philox_pre(traj_offset + rel, I.instance, R.key0, R.key1);
 
     // Groups below the kink, as in lanes_fp64: two steps' reach, with the noise S (xi_1, xi_2) and the bias
     // a S e (|e| <= 1) bounded by twice the largest entry of S.
@@ -1673,10 +1681,14 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
         2.0 * (fmax(1.4143, fabs(I.pi_in)) * dN + 2.0 * I.S_max * (fabs(a) * dN + 6.8 * sqrt_dN));
     const double phi_below = (dk.s_plus == dk.s_minus) ? __builtin_inf() : phi_T - reach;
 
-    // groups of two steps: one Philox call gives both steps' (xi_1, xi_2)
-    auto group = [&](auto censor_tag, auto below_tag, const double z[4]) {
+    // groups of two steps: one Philox call gives both steps' (xi_1, xi_2); without EVENTS as in lanes_fp64
+    auto group = [&](auto censor_tag, auto below_tag, auto events_tag, const double z[4]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool BELOW = decltype(below_tag)::value;
+        constexpr bool EVENTS = decltype(events_tag)::value;
+        const double phi0 = phi, pi0 = pi_, lnw0 = lnw;
+        bool any_end = false;
+        double eps1 = 0.0;          // pi^2/2 after the last step
         bool fresh = false;
         uint32_t ev_status, ev_n;   // written before use: read only where fresh is set
         double ev_N, ev_lnw;
@@ -1707,7 +1719,8 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
             const double B_pi = a * (S.Spq * S.e1 + S.Sqq * S.e2);
             const double phi_n =
                 (BIAS == kBiasNone) ? phi + pi_ * dN + noise_phi : phi + (pi_ + B_phi) * dN + noise_phi;
-            const double drift_pi = pi_ - (3.0 - 0.5 * pi_ * pi_) * (pi_ + r) * dN;
+            const double q_pi = (j == 0) ? fma(-pi_, 0.5 * pi_, 3.0) : 3.0 - eps1;      // as in lanes_fp64
+            const double drift_pi = pi_ - q_pi * (pi_ + r) * dN;
             const double pi_n = (BIAS == kBiasNone) ? drift_pi + noise_pi : drift_pi + B_pi * dN + noise_pi;
             if (BIAS != kBiasNone) {
                 const double dA = a * (S.e1 * z1 + S.e2 * z2) + half_a2_dN * (S.e1 * S.e1 + S.e2 * S.e2);
@@ -1715,7 +1728,10 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
                 else lnw -= (S.Spp != 0.0 || S.Spq != 0.0 || S.Sqq != 0.0) ? dA : 0.0;
             }
             // as in lanes_fp64
-            const bool hit = live & ((phi_n <= phi_end) | (0.5 * pi_n * pi_n >= 1.0));
+            eps1 = half_sq(pi_n);
+            const bool ends = (phi_n <= phi_end) | (eps1 >= 1.0);
+            const bool hit = EVENTS && (live & ends);
+            if (!EVENTS) any_end = any_end | ends;
             if (hit) {
                 double pa = phi, pb = phi_n;
                 uint32_t nb = n;
@@ -1732,8 +1748,46 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
             pi_ = pi_n;
             n += 1;
         }
+        if (!EVENTS) {
+            if (__builtin_amdgcn_ballot_w64(live && any_end) != 0) {
+                phi = phi0;
+                pi_ = pi0;
+                lnw = lnw0;
+                n -= 2;
+                return false;
+            }
+        }
         if (fresh) retire(rt, rel, ev_status, ev_n, ev_N, ev_lnw);
+        return true;
     };
+    auto run_group = [&](bool may_cap, const double z[4]) {
+        using Yes = std::integral_constant<bool, true>;
+        using No = std::integral_constant<bool, false>;
+        using Last = std::integral_constant<bool, !FEED>;      // paired waves: without events first
+        if (may_cap) group(Yes(), No(), Yes(), z);
+        else if (__builtin_amdgcn_ballot_w64(live && !(phi < phi_below)) == 0) {
+            if (!group(No(), Yes(), Last(), z)) group(No(), Yes(), Yes(), z);
+        } else if (!group(No(), No(), Last(), z)) group(No(), No(), Yes(), z);
+    };
+
+    if constexpr (FEED) {
+        const double2 *buf = reinterpret_cast<const double2 *>(feed.buf) + __lane_id();
+        for (uint32_t turn = 0;; ++turn) {
+            __syncthreads();
+            double2 v[kFeedSteps];
+#pragma unroll
+            for (int q = 0; q < kFeedSteps; ++q) v[q] = buf[64 * q];
+            feed.flags[(turn & 1) * kFeedMaxPairs + feed.pair] = __any(live) ? 1u : 0u;
+            if (!feed_goes_on(feed, turn)) break;
+            if (!__any(live)) continue;
+#pragma unroll
+            for (int q = 0; q < kFeedSteps; q += 2) {
+                const double z[4] = {v[q].x, v[q].y, v[q + 1].x, v[q + 1].y};
+                run_group((uint32_t)__builtin_amdgcn_readfirstlane(n) + 2 > I.max_steps, z);
+            }
+        }
+        return;
+    }
 
     while (__any(has)) {
         const uint32_t left = wave_steps_left(has, n, I.max_steps);
@@ -1744,11 +1798,7 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
             double z[4];
             box_muller64(w[0], w[1], sqrt_dN, l_bm, z[0], z[1]);
             box_muller64(w[2], w[3], sqrt_dN, l_bm, z[2], z[3]);
-            using Yes = std::integral_constant<bool, true>;
-            using No = std::integral_constant<bool, false>;
-            if ((uint32_t)k + 2 > left) group(Yes(), No(), z);
-            else if (__builtin_amdgcn_ballot_w64(live && !(phi < phi_below)) == 0) group(No(), Yes(), z);
-            else group(No(), No(), z);
+            run_group((uint32_t)k + 2 > left, z);
         }
         if (!live) has = false;
         if (claim(!has, rel, cursor, n_traj, exhausted)) {
@@ -1776,9 +1826,10 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
 // + a dN e), and dA = a e.xi sqrt(dN) + a^2 |e|^2 dN/2 is summed per group in
 // FP32 and across groups in FP64.
 // ---------------------------------------------------------------------------
-template <int BIAS, bool ALLPOS, bool TIME>
+template <int BIAS, bool ALLPOS, bool TIME, bool FEED = false>
 __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, const float4 *l_tab, const RetireTo &rt,
-                                              unsigned long long *cursor, uint64_t n_traj, uint64_t traj_offset)
+                                              unsigned long long *cursor, uint64_t n_traj, uint64_t traj_offset,
+                                              const Feed &feed = Feed{})
 {
     // steps per group: 16 (eight generator calls, the normals of the whole group formed first)
     constexpr int G = 16;
@@ -1793,14 +1844,15 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
     const float s_plus = in_vgpr(c.s_plus), s_minus = in_vgpr(c.s_minus);
 
     bool exhausted = false;
-    uint64_t rel = 0;
-    bool has = claim(true, rel, cursor, n_traj, exhausted);
+    uint64_t rel = FEED ? feed.first + __lane_id() : 0;
+    bool has = FEED ? rel < n_traj : claim(true, rel, cursor, n_traj, exhausted);
     bool live = has;
     float xh = x_in_hi, xl = x_in_lo, ph = pi_in_hi, pl = pi_in_lo;
     float xs = x_in_hi, ps = pi_in_hi;          // xs is formed each step only for a per-step lookup
     double lnw = 0.0;
     uint32_t n = 0;
-    PhiloxPre pre = philox_pre(traj_offset + rel, I.instance, R.key0, R.key1);
+    PhiloxPre pre{};
+    if (!FEED) pre = philox_pre(traj_offset + rel, I.instance, R.key0, R.key1);
 
     // Phi tables: the lane's group-start record, as in lanes_fp32: each entry's value at x = xh
     // and its slope per unit x, so that a step of a lane whose start interval is smooth evaluates
@@ -1810,9 +1862,13 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
 #pragma unroll
     for (int q = 0; q < 6; ++q) g_v[q] = g_d[q] = 0.0f;
 
-    auto group = [&](auto censor_tag, auto span_tag, const float z[2 * G]) {
+    // without EVENTS as in lanes_fp64
+    auto group = [&](auto censor_tag, auto span_tag, auto events_tag, const float z[2 * G]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool SPAN = decltype(span_tag)::value;
+        constexpr bool EVENTS = decltype(events_tag)::value;
+        const float xl0 = xl, pl0 = pl, xs0 = xs, ps0 = ps;
+        bool any_end = false;
         static_assert(!SPAN || (!TIME && !CENSOR), "one record per group: phi tables, no censoring");
         constexpr bool STEP_XS = !TIME && !SPAN;
         float zacc = 0.0f;        // this group's sum of dA
@@ -1885,7 +1941,8 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
             // x <= 0: the sign of a rounded sum is that of the exact one, so this is xs <= 0
             const bool crossed = xl <= -xh;
             const bool ended = fabsf(ps) >= 0x1.6a09e8p+0f;
-            const bool hit = live && (crossed || ended);
+            const bool hit = EVENTS && live && (crossed || ended);
+            if (!EVENTS) any_end = any_end | crossed | ended;
             if (hit) {
                 float bh = xh, b0 = x0l, b1 = xl, bz = zacc;
                 uint32_t nb = n + j;
@@ -1901,6 +1958,15 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
             live = live && !hit;
             fresh = fresh || hit;
         }
+        if (!EVENTS) {
+            if (__builtin_amdgcn_ballot_w64(live && any_end) != 0) {
+                xl = xl0;
+                pl = pl0;
+                xs = xs0;
+                ps = ps0;
+                return false;
+            }
+        }
         n += G;
         lnw -= (double)zacc;
         if (fresh) retire(rt, rel, ev_code & ~kStepMask, ev_code & kStepMask, ev_N, ev_lnw);
@@ -1909,8 +1975,63 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
         xh = xs;
         pl = pl - (ps - ph);
         ph = ps;
+        return true;
+    };
+    // One group from its normals; `may_cap`: a lane may reach max_steps in it.
+    auto run_group = [&](bool may_cap, const float z[2 * G]) {
+        using T = std::integral_constant<bool, true>;
+        using F = std::integral_constant<bool, false>;
+        using L = std::integral_constant<bool, !FEED>;         // paired waves: without events first
+        if constexpr (!TIME) {
+            // the record of the lane's interval at the group start
+            const float u0 = __builtin_amdgcn_fmed3f(fmaf(xh, c.inv_h, c.u_off), 0.0f, c.jtop);
+            const int j0 = (int)u0;
+            const float4 *rec = l_tab + 3 * j0;
+            const float4 A0 = rec[0], A1 = rec[1], A2 = rec[2];
+            const float fh = fmaf(xh, c.inv_h, c.u_off - (float)j0);   // the fraction at x = xh
+            const float v0[6] = {A0.x, A0.z, A1.x, A1.z, A2.x, A2.z};
+            const float d0[6] = {A0.y, A0.w, A1.y, A1.w, A2.y, A2.w};
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                g_v[q] = fmaf(fh, d0[q], v0[q]);
+                g_d[q] = d0[q] * c.inv_h;
+            }
+        }
+        if (may_cap) {
+            group(T(), F(), T(), z);
+        } else {
+            if constexpr (!TIME) {
+                if (__builtin_amdgcn_ballot_w64(live && g_v[5] != g_v[5]) == 0) {
+                    if (!group(F(), T(), L(), z)) group(F(), T(), T(), z);
+                } else {
+                    group(F(), F(), T(), z);
+                }
+            } else {
+                if (!group(F(), F(), L(), z)) group(F(), F(), T(), z);
+            }
+        }
     };
 
+    if constexpr (FEED) {
+        static_assert(G == kFeedSteps32, "a turn is one group");
+        const float4 *buf = reinterpret_cast<const float4 *>(feed.buf) + __lane_id();
+        for (uint32_t turn = 0;; ++turn) {
+            __syncthreads();
+            float z[2 * G];
+#pragma unroll
+            for (int q = 0; q < G / 2; ++q) {
+                const float4 v = buf[64 * q];
+                z[4 * q] = v.x;
+                z[4 * q + 1] = v.y;
+                z[4 * q + 2] = v.z;
+                z[4 * q + 3] = v.w;
+            }
+            feed.flags[(turn & 1) * kFeedMaxPairs + feed.pair] = __any(live) ? 1u : 0u;
+            if (!feed_goes_on(feed, turn)) break;
+            if (__any(live)) run_group((uint32_t)__builtin_amdgcn_readfirstlane(n) + G > I.max_steps, z);
+        }
+        return;
+    }
     while (__any(has)) {
         const uint32_t left = wave_steps_left(has, n, I.max_steps);
         for (int k = 0; k < R.chunk; k += G) {
@@ -1921,33 +2042,7 @@ __device__ __forceinline__ void lanes_fp32_2d(const Inst &I, const RunArgs &R, c
             float z[2 * G];
 #pragma unroll
             for (int q = 0; q < 2 * G; q += 2) box_muller32(w[q], w[q + 1], c.m2ln2_dN, 0.0f, z[q], z[q + 1]);
-            using T = std::integral_constant<bool, true>;
-            using F = std::integral_constant<bool, false>;
-            if constexpr (!TIME) {
-                // the record of the lane's interval at the group start
-                const float u0 = __builtin_amdgcn_fmed3f(fmaf(xh, c.inv_h, c.u_off), 0.0f, c.jtop);
-                const int j0 = (int)u0;
-                const float4 *rec = l_tab + 3 * j0;
-                const float4 A0 = rec[0], A1 = rec[1], A2 = rec[2];
-                const float fh = fmaf(xh, c.inv_h, c.u_off - (float)j0);   // the fraction at x = xh
-                const float v0[6] = {A0.x, A0.z, A1.x, A1.z, A2.x, A2.z};
-                const float d0[6] = {A0.y, A0.w, A1.y, A1.w, A2.y, A2.w};
-#pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    g_v[q] = fmaf(fh, d0[q], v0[q]);
-                    g_d[q] = d0[q] * c.inv_h;
-                }
-            }
-            if ((uint32_t)k + G > left) {
-                group(T(), F(), z);
-            } else {
-                if constexpr (!TIME) {
-                    if (__builtin_amdgcn_ballot_w64(live && g_v[5] != g_v[5]) == 0) group(F(), T(), z);
-                    else group(F(), F(), z);
-                } else {
-                    group(F(), F(), z);
-                }
-            }
+            run_group((uint32_t)k + G > left, z);
         }
         if (!live) has = false;
         if (claim(!has, rel, cursor, n_traj, exhausted)) {
@@ -1995,6 +2090,12 @@ __host__ __device__ __forceinline__ size_t align16(size_t b) { return (b + 15) &
 // FP64: double2 per node; FP32: float4 per node plus the float2 V'/V interval
 // LDS of a staged table: FP64 nodes (16 B) and the Box-Muller tables, or FP32 nodes and V'/V
 // intervals (24 B per node).
+// 2D noise.  FP64: three double2 per node and the Box-Muller tables; FP32: three float4 per node
+__host__ __device__ __forceinline__ size_t tab2d_bytes(int precision, int n_tab)
+{
+    return (size_t)(n_tab > 1 ? n_tab : 2) * 48 + (precision == 0 ? kBmBytes : 0);
+}
+
 __host__ __device__ __forceinline__ size_t tab_bytes(int precision, int n_tab)
 {
     return align16((size_t)(n_tab > 1 ? n_tab : 2) * (precision == 0 ? 16 : 24)) + (precision == 0 ? kBmBytes : 0);
@@ -2092,8 +2193,8 @@ __device__ __forceinline__ void pair_block(const Inst &I, const RunArgs &R, unsi
                                                        nullptr, n_traj, traj_offset, feed);
     } else {
         if (PREC == 0)
-            feed_fp64(I, R, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(I), traj_offset, feed);
-        else feed_fp32(I, R, traj_offset, feed);
+            feed_fp64<1>(I, R, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(I), traj_offset, feed);
+        else feed_fp32<1>(I, R, traj_offset, feed);
     }
     __syncthreads();
     flush_lds_acc(acc, I.acc);
@@ -2141,6 +2242,41 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em2d_kernel(EmParams p)
     else
         lanes_fp32_2d<BIAS, ALLPOS, TIME>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab), rt, p.cursor,
                                           p.n_traj, p.traj_offset);
+    __syncthreads();
+    flush_lds_acc(acc, p.inst.acc);
+}
+
+// A 2D-noise run on paired waves: pair_block with the 2D lanes and twice the buffer.
+template <int PREC, int BIAS, bool ALLPOS, bool TIME>
+__global__ void __launch_bounds__(64 * 2 * kFeedMaxPairs) em2d_pair_kernel(EmParams p)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint32_t flags[2 * kFeedMaxPairs];
+    const LdsAcc acc = lds_acc(smem, p.inst.hist.n_bins);
+    unsigned char *l_tab = smem + align16(acc_bytes(p.inst.hist.n_bins));
+    unsigned char *l_feed = l_tab + tab2d_bytes(PREC, p.inst.n_tab);
+    zero_lds_acc(acc);
+    if (PREC == 0) stage_table64_2d(p.inst, reinterpret_cast<double2 *>(l_tab));
+    else stage_table32_2d(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
+    __syncthreads();
+    const RetireTo rt = retire_to(p, acc);
+    const int wave = (int)(__builtin_amdgcn_readfirstlane(threadIdx.x) / 64), pairs = (int)(blockDim.x / 128);
+    const int pair = wave < pairs ? wave : wave - pairs;
+    const Feed feed{l_feed + (size_t)pair * 2 * kFeedBytes, flags, pair, pairs,
+                    (uint64_t)blockIdx.x * (blockDim.x / 2) + (uint64_t)pair * 64};
+    if (wave < pairs) {
+        if (PREC == 0)
+            lanes_fp64_2d<BIAS, ALLPOS, TIME, true>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab), rt, nullptr,
+                                                    p.n_traj, p.traj_offset, feed);
+        else
+            lanes_fp32_2d<BIAS, ALLPOS, TIME, true>(p.inst, p.run, reinterpret_cast<const float4 *>(l_tab), rt, nullptr,
+                                                    p.n_traj, p.traj_offset, feed);
+    } else {
+        if (PREC == 0)
+            feed_fp64<2>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab) + 3 * staged_nodes(p.inst),
+                         p.traj_offset, feed);
+        else feed_fp32<2>(p.inst, p.run, p.traj_offset, feed);
+    }
     __syncthreads();
     flush_lds_acc(acc, p.inst.acc);
 }
@@ -2436,8 +2572,7 @@ hipError_t em_launch(const EmParams &p, int precision, int grid, int block, hipS
 
 size_t em2d_lds_bytes(int n_bins, int n_tab, int precision)
 {
-    // FP64: three double2 per node and the Box-Muller tables; FP32: three float4 per node
-    return align16(acc_bytes(n_bins)) + (size_t)(n_tab > 1 ? n_tab : 2) * 48 + (precision == 0 ? kBmBytes : 0);
+    return align16(acc_bytes(n_bins)) + tab2d_bytes(precision, n_tab);
 }
 
 template <int PREC, int BIAS>
@@ -2454,6 +2589,25 @@ const void *em2d_kernel_ptr(int precision, int bias_kind, bool all_pos, bool tim
     static const K2Tab<0, kBiasConst> d_c;
     static const K2Tab<1, kBiasNone> f_n;
     static const K2Tab<1, kBiasConst> f_c;
+    const bool c = bias_kind != kBiasNone;
+    const void *const(*t)[2] = precision == 0 ? (c ? d_c.p : d_n.p) : (c ? f_c.p : f_n.p);
+    return t[all_pos ? 1 : 0][time_axis ? 1 : 0];
+}
+
+template <int PREC, int BIAS>
+struct P2Tab {
+    const void *p[2][2] = {{reinterpret_cast<const void *>(&em2d_pair_kernel<PREC, BIAS, false, false>),
+                            reinterpret_cast<const void *>(&em2d_pair_kernel<PREC, BIAS, false, true>)},
+                           {reinterpret_cast<const void *>(&em2d_pair_kernel<PREC, BIAS, true, false>),
+                            reinterpret_cast<const void *>(&em2d_pair_kernel<PREC, BIAS, true, true>)}};
+};
+
+const void *em2d_pair_kernel_ptr(int precision, int bias_kind, bool all_pos, bool time_axis)
+{
+    static const P2Tab<0, kBiasNone> d_n;
+    static const P2Tab<0, kBiasConst> d_c;
+    static const P2Tab<1, kBiasNone> f_n;
+    static const P2Tab<1, kBiasConst> f_c;
     const bool c = bias_kind != kBiasNone;
     const void *const(*t)[2] = precision == 0 ? (c ? d_c.p : d_n.p) : (c ? f_c.p : f_n.p);
     return t[all_pos ? 1 : 0][time_axis ? 1 : 0];

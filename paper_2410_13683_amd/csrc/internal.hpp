@@ -167,8 +167,8 @@ const void *em_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_p
 hipError_t em_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream,
                      bool mlp_exact = false);
 // The paired-wave variant for runs of at most 64 kFeedMaxPairs trajectories per CU (bias none or
-// constant, 1D noise; nullptr otherwise): blocks of up to kFeedMaxPairs pairs of waves, kFeedBytes of
-// LDS per pair after em_lds_bytes.  kFeedSteps (FP64) or kFeedSteps32 steps' normals are handed over at a time.
+// constant; nullptr otherwise): blocks of up to kFeedMaxPairs pairs of waves, kFeedBytes of
+// LDS per pair after em_lds_bytes (2D noise: em2d_pair_kernel, twice that).  kFeedSteps (FP64) or kFeedSteps32 steps' normals are handed over at a time.
 constexpr int kFeedMaxPairs = 8, kFeedSteps = 8, kFeedSteps32 = 16;
 constexpr size_t kFeedBytes = 64 * kFeedSteps * sizeof(double);
 constexpr size_t kFeedFlagBytes = 2 * kFeedMaxPairs * sizeof(uint32_t);
@@ -176,6 +176,7 @@ static_assert(kFeedBytes == 64 * kFeedSteps32 * sizeof(float), "one buffer size 
 const void *em_pair_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_pos, int pot_kind);
 const void *replay_kernel_ptr(int precision, bool all_pos);
 size_t em2d_lds_bytes(int n_bins, int n_tab, int precision);
+const void *em2d_pair_kernel_ptr(int precision, int bias_kind, bool all_pos, bool time_axis);
 const void *em2d_kernel_ptr(int precision, int bias_kind, bool all_pos, bool time_axis);
 hipError_t em2d_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream);
 hipError_t replay_launch(const ReplayParams &p, int precision, int grid, int block, hipStream_t stream);
