@@ -772,6 +772,26 @@ static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_tr
     return FPT_OK;
 }
 
+// Pairs of waves per block with which a run of n_traj trajectories takes a paired-wave kernel (em_pair_kernel,
+// em2d_pair_kernel, the paired em_record_kernel; `lds` bytes before the pairs' buffers of pair_bytes each), or 0:
+// up to kFeedMaxPairs pairs per CU, i.e. two integrating waves per SIMD, whose partners fill its other two.
+// 65,536 trajectories (slow roll -> ultra-slow roll) take 7.1 against 9.7 ms unpaired in FP32 state (10.8
+// against 16.6 on the e-fold axis) and 16.7 against 22.1 ms in FP64, 131,072 take 10.0 against 11.9 and 27.4
+// against 30.2 ms, 1e4 of the linear problem 0.79 against 1.28 ms; with 2D noise 32,768 take 19.6 against 36.9
+// ms in FP64 and 8.6 against 13.3 in FP32 state, 65,536 26.5 against 34.4 and 10.9 against 13.2.  Beyond, four
+// integrating waves per SIMD keep it busy by themselves, and with 2D noise a table of 2048 nodes leaves no
+// LDS for eight pairs.  Odd counts above 4 are rounded up: seven pairs took longer than eight (12.1 against
+// 10.7 ms).
+static int wave_pairs(const fpt_ctx *c, uint64_t n_traj, size_t lds, size_t pair_bytes)
+{
+    if (c->opt.block_size || c->opt.blocks_per_cu) return 0;
+    const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
+    uint64_t pairs = (waves + cus - 1) / cus;
+    if (pairs > 4) pairs += pairs & 1;
+    if (pairs > (uint64_t)kFeedMaxPairs || lds + pairs * pair_bytes + kFeedFlagBytes > c->lds_per_block_max) return 0;
+    return (int)pairs;
+}
+
 extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset,
                        void *hip_stream, double *d_N, double *d_lnw, uint32_t *d_steps)
 {
@@ -810,21 +830,10 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
                                             exact);
     const int rc = run_shape(c, fn, lds, n_traj, grid, block, exact && c->precision == FPT_FP32_STATE ? kMaxBlockNet32 : 1024);
     if (rc) return rc;
-    // Paired waves (em_pair_kernel, em2d_pair_kernel) up to 64 kFeedMaxPairs trajectories per CU, i.e. two integrating waves per
-    // SIMD, whose partners fill its other two: 65,536 trajectories (slow roll -> ultra-slow roll) take 7.1
-    // against 9.7 ms unpaired in FP32 state (10.8 against 16.6 on the e-fold axis) and 17.3 against 22.2 ms in
-    // FP64, 131,072 take 10.0 against 11.8 and 28.1 against 30.2 ms, 1e4 of the linear problem 0.81 against
-    // 1.30 ms; with 2D noise 32,768 take 19.6 against 36.9 ms in FP64 and 8.6 against 13.3 in FP32 state,
-    // 65,536 26.5 against 34.4 and 10.9 against 13.2 (beyond, a table of 2048 nodes leaves no LDS for the
-    // buffers of more than five pairs); beyond, four integrating waves per SIMD keep it busy by themselves.  Odd counts above 4 are
-    // rounded up: seven pairs took longer than eight (12.1 against 10.7 ms).
-    const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
-    uint64_t pairs = (waves + cus - 1) / cus;
-    if (pairs > 4) pairs += pairs & 1;
-    const size_t pair_lds = lds + pairs * (two_d ? 2 : 1) * kFeedBytes;
     const void *pair_fn = nullptr;
-    if (!c->opt.block_size && !c->opt.blocks_per_cu && pairs <= (uint64_t)kFeedMaxPairs &&
-        pair_lds + kFeedFlagBytes <= c->lds_per_block_max)
+    const size_t pair_bytes = (two_d ? 2 : 1) * kFeedBytes;
+    const int pairs = wave_pairs(c, n_traj, lds, pair_bytes);
+    if (pairs)
         pair_fn = two_d ? em2d_pair_kernel_ptr(c->precision, c->inst.bias_kind, c->inst.all_S_pos != 0,
                                                tab_mode(c->inst) == 2)
                         : em_pair_kernel_ptr(c->precision, bias_k, tab_mode(c->inst), c->inst.all_S_pos != 0,
@@ -832,8 +841,8 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     if (pair_fn) {
         HIP_TRY(hipEventRecord(c->ev_start, s));
         void *args[] = {&p};
-        HIP_TRY(hipLaunchKernel(pair_fn, dim3((unsigned)((waves + pairs - 1) / pairs)), dim3((unsigned)(128 * pairs)),
-                                args, pair_lds, s));
+        HIP_TRY(hipLaunchKernel(pair_fn, dim3((unsigned)((n_traj + 64 * pairs - 1) / (64 * pairs))),
+                                dim3((unsigned)(128 * pairs)), args, lds + pairs * pair_bytes, s));
         HIP_TRY(hipEventRecord(c->ev_stop, s));
         HIP_TRY(hipEventRecord(c->ev_done, s));
         c->ran = true;
@@ -1083,7 +1092,7 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
     const int block = c->opt.block_size ? c->opt.block_size : 1024;
     int grid_rp = 0;
     const int n_cells = grid_cells(c->inst);
-    const void *em_fn = rec ? em_record_kernel_ptr(c->precision, tab_mode(c->inst), c->inst.all_S_pos != 0)
+    const void *em_fn = rec ? em_record_kernel_ptr(c->precision, tab_mode(c->inst), c->inst.all_S_pos != 0, false)
                             : em_kernel_ptr(c->precision, kBiasMlp, tab_mode(c->inst), c->inst.all_S_pos != 0);
     const size_t em_lds = em_lds_bytes(c->opt.n_bins, c->inst.n_tab, c->precision, n_cells);
     rc = occupancy_grid(replay_kernel_ptr(c->precision, c->inst.all_S_pos != 0), block,
@@ -1110,7 +1119,12 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
         rc = run_shape(c, em_fn, em_lds, m, grid_em, block_em);
         if (rc) return rc;
         if (rec) {
-            HIP_TRY(em_record_launch(p, *rec, c->precision, grid_em, block_em, s));
+            const int pairs = wave_pairs(c, m, em_lds, kFeedBytes);
+            if (pairs) {
+                block_em = 128 * pairs;
+                grid_em = (int)((m + 64 * pairs - 1) / (64 * pairs));
+            }
+            HIP_TRY(em_record_launch(p, *rec, c->precision, grid_em, block_em, pairs, s));
             HIP_TRY(tail_weigh(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, *rec, c->precision,
                                g.n0, g.n1, c->d_G, d_tail, &cnt[0], &cnt[1], c->d_J, c->cu_count, s));
         } else {

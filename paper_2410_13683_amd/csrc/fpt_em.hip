@@ -1019,7 +1019,8 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     // The group's variant from its normals; `may_cap`: a lane may reach max_steps in it.
     auto noisy_group = [&](bool may_cap, const double z[4]) {
         using Below = std::integral_constant<bool, CAN_BELOW>;
-        using Last = std::integral_constant<bool, !FEED>;      // paired waves: without events first
+        // paired waves: without events first, unless a step leaves records behind
+        using Last = std::integral_constant<bool, !FEED || GRAD != kGradNone>;
         if (may_cap) group(Yes(), No(), No(), Yes(), z);
         else if (CAN_BELOW && all_below()) {
             if (!group(No(), Below(), No(), Last(), z)) group(No(), Below(), No(), Yes(), z);
@@ -1495,7 +1496,8 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
     auto run_group = [&](bool may_cap, const float z[G]) {
         using T = std::integral_constant<bool, true>;
         using F = std::integral_constant<bool, false>;
-        using L = std::integral_constant<bool, !FEED>;         // paired waves: without events first
+        // paired waves: without events first, unless a step leaves records behind
+        using L = std::integral_constant<bool, !FEED || GRAD != kGradNone>;
         if constexpr (TAB == 1) {
             // the record of the lane's interval at the group start
             const float u0 = __builtin_amdgcn_fmed3f(fmaf(xs, c.inv_h, c.u_off), 0.0f, c.jtop);
@@ -1517,7 +1519,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
                 if (__builtin_amdgcn_ballot_w64(live && g_r != g_r) != 0) {
                     group(F(), F(), T(), T(), z);
                 } else if constexpr (LEARNED) {
-                    group(F(), T(), T(), T(), z);
+                    if (!group(F(), T(), T(), L(), z)) group(F(), T(), T(), T(), z);
                 } else {
                     if (__builtin_amdgcn_ballot_w64(live && fabsf(ps) > pi_safe) == 0) {
                         if (!group(F(), T(), F(), L(), z)) group(F(), T(), F(), T(), z);
@@ -2320,7 +2322,9 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY replay_kernel(ReplayPar
 }
 
 // Recording run: em_kernel's tabulated control, with each path's gradient sums per visited cell kept.
-template <int PREC, int TAB, bool ALLPOS>
+// PAIRED: on paired waves, as em_pair_kernel (a training step on 5000 trajectories 20.4 -> 18.4 ms, on
+// 100,000 25.3 -> 21.6; the integrating wave, some 440 cycles a step with its cell's sums, is the longer side).
+template <int PREC, int TAB, bool ALLPOS, bool PAIRED>
 __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em_record_kernel(EmParams p, RecordPool rec)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2334,7 +2338,28 @@ __global__ void __launch_bounds__(1024) FPT_EM_OCCUPANCY em_record_kernel(EmPara
     __syncthreads();
     const RetireTo rt = retire_to(p, acc);
     const ReplayTo rp{nullptr, nullptr, nullptr, rec};
-    if (PREC == 0)
+    if (PAIRED) {
+        __shared__ uint32_t flags[2 * kFeedMaxPairs];
+        unsigned char *l_feed = l_grid + cell_bytes(PREC, grid_cells(p.inst));
+        const int wave = (int)(__builtin_amdgcn_readfirstlane(threadIdx.x) / 64), pairs = (int)(blockDim.x / 128);
+        const int pair = wave < pairs ? wave : wave - pairs;
+        const Feed feed{l_feed + (size_t)pair * kFeedBytes, flags, pair, pairs,
+                        (uint64_t)blockIdx.x * (blockDim.x / 2) + (uint64_t)pair * 64};
+        if (wave >= pairs) {
+            if (PREC == 0)
+                feed_fp64<1>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab) + staged_nodes(p.inst),
+                             p.traj_offset, feed);
+            else feed_fp32<1>(p.inst, p.run, p.traj_offset, feed);
+        } else if (PREC == 0) {
+            lanes_fp64<kBiasMlp, TAB, ALLPOS, kGradRecord, kPotPiecewiseLinear, true>(
+                p.inst, p.run, reinterpret_cast<const double2 *>(l_tab), reinterpret_cast<const double2 *>(l_grid), rt,
+                rp, nullptr, p.n_traj, p.traj_offset, feed);
+        } else {
+            lanes_fp32<kBiasMlp, TAB, ALLPOS, kGradRecord, true>(
+                p.inst, p.run, reinterpret_cast<const float4 *>(l_tab), reinterpret_cast<const float4 *>(l_grid), rt, rp,
+                nullptr, p.n_traj, p.traj_offset, feed);
+        }
+    } else if (PREC == 0)
         lanes_fp64<kBiasMlp, TAB, ALLPOS, kGradRecord>(p.inst, p.run, reinterpret_cast<const double2 *>(l_tab),
                                                        reinterpret_cast<const double2 *>(l_grid), rt, rp, p.cursor,
                                                        p.n_traj, p.traj_offset);
@@ -2639,30 +2664,33 @@ hipError_t replay_launch(const ReplayParams &p, int precision, int grid, int blo
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, stream);
 }
 
-template <int PREC>
+template <int PREC, bool PAIRED>
 const void *rptr(int tab_mode, bool all_pos)
 {
-    static const void *const t[2][2] = {{reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, false>),
-                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, true>)},
-                                        {reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, false>),
-                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, true>)}};
+    static const void *const t[2][2] = {{reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, false, PAIRED>),
+                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 0, true, PAIRED>)},
+                                        {reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, false, PAIRED>),
+                                         reinterpret_cast<const void *>(&em_record_kernel<PREC, 1, true, PAIRED>)}};
     return t[tab_mode ? 1 : 0][all_pos ? 1 : 0];
 }
 
-const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos)
+const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos, bool paired)
 {
-    return precision == 0 ? rptr<0>(tab_mode, all_pos) : rptr<1>(tab_mode, all_pos);
+    if (paired) return precision == 0 ? rptr<0, true>(tab_mode, all_pos) : rptr<1, true>(tab_mode, all_pos);
+    return precision == 0 ? rptr<0, false>(tab_mode, all_pos) : rptr<1, false>(tab_mode, all_pos);
 }
 
-hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block,
+hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block, int pairs,
                             hipStream_t stream)
 {
     EmParams pp = p;
     RecordPool rr = rec;
     void *args[] = {&pp, &rr};
-    return hipLaunchKernel(em_record_kernel_ptr(precision, tab_mode(p.inst), p.inst.all_S_pos != 0), dim3(grid),
-                           dim3(block), args,
-                           em_lds_bytes(p.inst.hist.n_bins, p.inst.n_tab, precision, grid_cells(p.inst)), stream);
+    return hipLaunchKernel(em_record_kernel_ptr(precision, tab_mode(p.inst), p.inst.all_S_pos != 0, pairs > 0),
+                           dim3(grid), dim3(block), args,
+                           em_lds_bytes(p.inst.hist.n_bins, p.inst.n_tab, precision, grid_cells(p.inst)) +
+                               pairs * kFeedBytes,
+                           stream);
 }
 
 hipError_t tail_weigh(const double *d_N, const double *d_lnw, const uint32_t *d_steps, uint64_t n,

@@ -181,8 +181,9 @@ const void *em2d_kernel_ptr(int precision, int bias_kind, bool all_pos, bool tim
 hipError_t em2d_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream);
 hipError_t replay_launch(const ReplayParams &p, int precision, int grid, int block, hipStream_t stream);
 // Recording runs (the tabulated control; tab_mode 0 or 1) and the weighting of their tail (see fpt_em.hip).
-const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos);
-hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block,
+const void *em_record_kernel_ptr(int precision, int tab_mode, bool all_pos, bool paired);
+// pairs > 0: on paired waves, `grid` blocks of `pairs` pairs (block = 128 pairs threads) covering p.n_traj
+hipError_t em_record_launch(const EmParams &p, const RecordPool &rec, int precision, int grid, int block, int pairs,
                             hipStream_t stream);
 hipError_t tail_weigh(const double *d_N, const double *d_lnw, const uint32_t *d_steps, uint64_t n,
                       uint64_t traj_offset, double N_ref, double tail_lo, const RecordPool &rec, int precision, int n0,
