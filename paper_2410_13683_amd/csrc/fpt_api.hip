@@ -17,6 +17,9 @@
 #include <vector>
 #include <limits>
 #include <mutex>
+#include <initializer_list>
+#include <memory>
+#include <new>
 
 using namespace fpt;
 
@@ -107,6 +110,25 @@ __global__ void table_bessel_kernel(PotParams pp, double sigma, int n, double ph
     t[j] = nu - 1.5;   // Xi_phipi / Xi_phiphi
 }
 
+// A table generator's output, arrays of n doubles one after another (those with a host array in `out` are
+// wanted) and the status word behind them, in one copy: each further one cost about 12 us of a call whose
+// kernels take 10 to 1000.
+static hipError_t read_table(const double *d, int n, std::initializer_list<double *> out, int &status)
+{
+    const size_t bytes = out.size() * n * sizeof(double) + sizeof(int);
+    std::unique_ptr<unsigned char[]> h(new (std::nothrow) unsigned char[bytes]);
+    if (!h) return hipErrorOutOfMemory;
+    const hipError_t e = hipMemcpy(h.get(), d, bytes, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return e;
+    const unsigned char *from = h.get();
+    for (double *o : out) {
+        if (o) std::memcpy(o, from, n * sizeof(double));
+        from += n * sizeof(double);
+    }
+    std::memcpy(&status, from, sizeof(int));
+    return hipSuccess;
+}
+
 extern "C" int fpt_noise_table_bessel(const fpt_potential *pot, double sigma, int32_t n, double phi_lo,
                                       double phi_hi, double *S_out, double *tan_out)
 {
@@ -129,9 +151,7 @@ extern "C" int fpt_noise_table_bessel(const fpt_potential *pot, double sigma, in
         e = hipGetLastError();
     }
     int bad = 0;
-    if (e == hipSuccess) e = hipMemcpy(S_out, d, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(tan_out, d + n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_table(d, n, {S_out, tan_out}, bad);
     (void)hipFree(d);
     if (e != hipSuccess) return hip_fail(e, "noise table kernel");
     if (bad) return fail(FPT_EINVAL, "V <= 0 or nu^2 <= 0 at a table node");
@@ -171,10 +191,7 @@ extern "C" int fpt_noise_table_bessel2d(const fpt_potential *pot, double sigma, 
         e = hipGetLastError();
     }
     int bad = 0;
-    if (e == hipSuccess) e = hipMemcpy(Xpp_out, d, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(Xpq_out, d + n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(Xqq_out, d + 2 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&bad, d_bad, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_table(d, n, {Xpp_out, Xpq_out, Xqq_out}, bad);
     (void)hipFree(d);
     if (e != hipSuccess) return hip_fail(e, "2D noise table kernel");
     if (bad) return fail(FPT_EINVAL, "V <= 0, nu^2 <= 0 or nu near an integer at a table node");
@@ -208,10 +225,7 @@ extern "C" int fpt_noise_table_matched(const fpt_potential *pot, double sigma, i
         e = fpt::matched_table_launch(pot_params(*pot), sigma, n, phi_lo, h, phi_start, pi_start, d, d_S, d_S + n,
                                       d_S + 2 * n, d_status, nullptr);
     int status = 0;
-    if (e == hipSuccess) e = hipMemcpy(S_out, d_S, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(tan_out, d_S + n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && fac_out) e = hipMemcpy(fac_out, d_S + 2 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&status, d_status, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_table(d_S, n, {S_out, tan_out, fac_out}, status);
     (void)hipFree(d);
     if (e != hipSuccess) return hip_fail(e, "matched noise table kernels");
     if (status & 1) return fail(FPT_EINVAL, "V <= 0 or nu^2 <= 0 at a table node");
@@ -248,11 +262,7 @@ extern "C" int fpt_noise_table_matched_time(const fpt_potential *pot, double sig
         e = fpt::matched_time_launch(pot_params(*pot), sigma, n, t_lo, h, phi_start, pi_start, phi_ref, N_after, d,
                                      d_S, d_S + n, d_S + 2 * n, d_S + 3 * n, d_status, nullptr);
     int status = 0;
-    if (e == hipSuccess) e = hipMemcpy(S_out, d_S, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(tan_out, d_S + n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && fac_out) e = hipMemcpy(fac_out, d_S + 2 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && phi_out) e = hipMemcpy(phi_out, d_S + 3 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&status, d_status, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_table(d_S, n, {S_out, tan_out, fac_out, phi_out}, status);
     (void)hipFree(d);
     if (e != hipSuccess) return hip_fail(e, "time-node matched noise table kernels");
     if (status & 16)
@@ -291,11 +301,7 @@ extern "C" int fpt_noise_table_bessel2d_time(const fpt_potential *pot, double si
         e = fpt::bessel2d_time_launch(pot_params(*pot), sigma, n, t_lo, h, phi_start, pi_start, phi_ref, N_after, d,
                                       d_X, d_X + n, d_X + 2 * n, d_X + 3 * n, d_status, nullptr);
     int status = 0;
-    if (e == hipSuccess) e = hipMemcpy(Xpp_out, d_X, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(Xpq_out, d_X + n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(Xqq_out, d_X + 2 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess && phi_out) e = hipMemcpy(phi_out, d_X + 3 * n, sizeof(double) * n, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&status, d_status, sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = read_table(d_X, n, {Xpp_out, Xpq_out, Xqq_out, phi_out}, status);
     (void)hipFree(d);
     if (e != hipSuccess) return hip_fail(e, "time-node 2D noise table kernels");
     if (status & 16)
