@@ -92,9 +92,9 @@ PEAK_HBM_GBS = 8000.0
 # process (FETCH_SIZE reads 0.5 GiB: x2.0; WRITE_SIZE reads 1 GiB: x1.0).  Valid only for the
 # kernel source it was measured on (hash of the kernel file and its header).
 MEASURED_TRAFFIC = {
-    "source_sha256": "aed86ebbd51f7c296c382842ad6b44d78e6aef024838dc47c5fdef1a441325f3",
+    "source_sha256": "0bca8a505e2c731396a9a69d5a1d2477a2c416b93f81a96f1921b89c18680690",
     "workload": "srusr_is_fp32_A2", "n_traj": 100_000_000,
-    "fetch_bytes": 10924.75 * 1024 * 2.0, "write_bytes": 2126993.28125 * 1024 * 1.0,
+    "fetch_bytes": 10931.4375 * 1024 * 2.0, "write_bytes": 2127300.90625 * 1024 * 1.0,
 }
 
 
@@ -143,16 +143,16 @@ def kernel_source_sha() -> str:
 # 2 FMA + ADD + MUL + TRANS of each precision.  They measure what the compiled kernel executes,
 # beside the operation-by-operation count of the method used for "achieved".
 MEASURED_VALU = {
-    "source_sha256": "aed86ebbd51f7c296c382842ad6b44d78e6aef024838dc47c5fdef1a441325f3",
-    "srusr_is_fp32_A2": {"VALUBusy": 138.967, "VALUUtilization": 98.989,
+    "source_sha256": "0bca8a505e2c731396a9a69d5a1d2477a2c416b93f81a96f1921b89c18680690",
+    "srusr_is_fp32_A2": {"VALUBusy": 139.173, "VALUUtilization": 98.989,
                          "hw_flops_per_step": {"f32": 27.720, "f64": 0.143},
                          "insts_per_step": {"FMA_F32": 10.351, "ADD_F32": 3.325, "MUL_F32": 1.689,
                                             "TRANS_F32": 2.003, "CVT": 1.263, "INT32": 0.625,
                                             "FMA_F64": 0.025, "ADD_F64": 0.094}},
-    "srusr_bessel_fp64": {"VALUBusy": 94.003, "VALUUtilization": 99.732,
-                          "hw_flops_per_step": {"f32": 0.0, "f64": 57.127},
-                          "insts_per_step": {"FMA_F64": 19.968, "ADD_F64": 5.311, "MUL_F64": 10.364,
-                                             "TRANS_F64": 1.517, "INT32": 4.934, "FMA_F32": 0.0,
+    "srusr_bessel_fp64": {"VALUBusy": 93.582, "VALUUtilization": 99.732,
+                          "hw_flops_per_step": {"f32": 0.0, "f64": 57.052},
+                          "insts_per_step": {"FMA_F64": 19.942, "ADD_F64": 5.304, "MUL_F64": 10.350,
+                                             "TRANS_F64": 1.515, "INT32": 4.928, "FMA_F32": 0.0,
                                              "ADD_F32": 0.0, "MUL_F32": 0.0}},
 }
 # the issue rate of independent v_fma_f32 chains, wave-instructions per SIMD per cycle, recorded
