@@ -22,7 +22,7 @@ namespace fpt {
 namespace {
 
 constexpr double kBgStep = 1e-4;         // e-folds between trajectory samples
-constexpr double kBgMaxN = 200.0;        // the trajectory is followed at most this long
+constexpr int kBgLast = 2000000;         // the trajectory's last sample at most: 200 e-folds
 constexpr double kModeMaxStep = 2.5e-4;  // largest RK4 step of a mode, in e-folds
 constexpr double kStepsPerPeriod = 800.0;
 constexpr double kStartRatio = 100.0;    // a mode starts at k = 100 aH
@@ -237,6 +237,7 @@ struct MacroRec {
     double phi, pi_;
 };
 constexpr int kMacroCap = 1 << 16;
+static_assert(kBgLast < kMatchCap, "room for every sample");
 
 // The last sample and the number of strides; the first sample at which the trajectory ended, and the
 // first at or below phi_ref (INT_MAX if none).
@@ -271,10 +272,12 @@ __device__ inline void put_sample(const BgStore &b, int i, double N, Bg y)
 // The chain is bound by latency: 3.3e5 dependent RK4 steps (33 e-folds) took 314 ms on one thread; the
 // strides of 16 dependent evaluations take 0.29 ms, and the samples between them 0.03 ms (bg_fill_kernel).
 // stop_phi: the samples end once phi < stop_phi (phi nodes; -inf for time nodes).  ref_phi: they
-// end N_after e-folds after phi first reached ref_phi (time nodes; -inf for phi nodes).
+// end N_after e-folds after phi first reached ref_phi (time nodes; -inf for phi nodes).  A stride may pass
+// these ends (bg_scan_kernel finds the sample), but the last one is cut at kBgLast: what lies beyond is
+// not part of the trajectory.
 template <int KIND>
 __global__ void __launch_bounds__(64) bg_macro_kernel(Pot pot, double phi_start, double pi_start, double stop_phi,
-                                                      double ref_phi, double N_after, int cap, BgStore b)
+                                                      double ref_phi, double N_after, BgStore b)
 {
     constexpr double kTol = 1e-12, kSmooth = 3e-14;
     constexpr int kHold = 6;
@@ -287,12 +290,12 @@ __global__ void __launch_bounds__(64) bg_macro_kernel(Pot pot, double phi_start,
     int i = 0, m = m_max, nrec = 0, hold = 0;
     double N = 0.0, N_end = INFINITY;
     if (lane == 0) put_sample(b, 0, N, y);
-    while (!(y.phi < stop_phi || 0.5 * y.pi_ * y.pi_ >= 1.0 || N > kBgMaxN || i + 1 >= cap || N >= N_end)) {
+    while (!(y.phi < stop_phi || 0.5 * y.pi_ * y.pi_ >= 1.0 || i >= kBgLast || N >= N_end)) {
         const bool upper = linear && y.phi > p.phi_T;
         // a state that is no number stays one: the remaining samples are filled with it
         const bool lost = nrec < kMacroCap && !(fabs(y.phi) < INFINITY && fabs(y.pi_) < INFINITY);
-        const int room = cap - 1 - i;
-        if (m > room) m = 1;
+        const int room = kBgLast - i;
+        if (m > room) m = room;
         if (nrec >= kMacroCap) m = 1;
         Bg z = y;
         bool take = m == 1 || lost;
@@ -325,7 +328,7 @@ __global__ void __launch_bounds__(64) bg_macro_kernel(Pot pot, double phi_start,
             ++nrec;
             N += H;
         } else if (lost) {
-            m = (int)fmax(1.0, fmin((double)room, floor((kBgMaxN - N) / kBgStep) + 2.0));
+            m = room;
             if (lane == 0) b.rec[nrec] = MacroRec{i, i + m, 0, 0, y.phi, y.pi_};
             ++nrec;
             N += (double)m * kBgStep;
@@ -805,11 +808,11 @@ hipError_t bg_launch(const PotParams &p, double phi_start, double pi_start, doub
                  : p.kind == kPotExponential   ? bg_macro_kernel<kPotExponential>
                                                : bg_macro_kernel<kPotGaussianBump>;
     hipLaunchKernelGGL(macro, dim3(1), dim3(64), 0, stream, p, phi_start, pi_start, stop_phi, ref_phi, N_after,
-                       (int)kMatchCap, b);
+                       b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the sample count is on the device: grids for the longest trajectory, whose excess blocks end at once
-    const int most = (int)(kBgMaxN / kBgStep) + 2;
+    const int most = kBgLast + 1;
     const int per_block = 256 * kFillChunk;
     hipLaunchKernelGGL(bg_fill_kernel, dim3((most + per_block - 1) / per_block), dim3(256), 0, stream, p, b);
     e = hipGetLastError();
