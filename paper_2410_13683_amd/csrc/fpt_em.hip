@@ -1276,13 +1276,15 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
     // table and the largest |V'/V| between phi_end and the kink, where it is monotonic): its steps need no
     // clamp, no branch select, no test of S and no end test, and n + j is exact in FP32.  Eight operations
     // fewer of some fifty per step: 1e6 trajectories of the time-indexed problem 124.5 -> 104.8 ms.
+    // With equal slopes there is no kink to stay below, as long as |V'/V| does not grow upwards either
+    // (V' >= 0, or the exponential potential); V' < 0 keeps the lanes below phi_T, up to which the bound holds.
     const float z_most = fmaf(6.8f, __builtin_amdgcn_sqrtf(c.dN), fabsf((float)A) * c.dN);
     const float reach = 1.01f * 16.0f * fmaf((float)I.S_max, z_most, fmaxf(1.4143f, fabsf((float)I.pi_in)) * c.dN);
-    const float below = (c.s_plus == c.s_minus) ? __builtin_inff() : -reach;
+    const float d_end = fmaf(-(c.xT_hi + c.xT_lo), c.kx, c.s_minus);      // 1/((V'/V) dN/2) at phi_end
+    const float below = (c.s_plus == c.s_minus && (c.kx == 0.0f || d_end > 0.0f)) ? __builtin_inff() : -reach;
     const float u_plain = (float)(I.n_pos - 1);
     float pi_plain = -1.0f;
     if (TAB == 2) {
-        const float d_end = fmaf(-(c.xT_hi + c.xT_lo), c.kx, c.s_minus);
         const float r_most = 1.01f / fminf(fabsf(c.s_minus), fabsf(d_end));
         const float delta = fmaf(6.0f, fmaf(0.7072f, c.dN, r_most), (float)(I.t_max * I.S_max) * z_most);
         if (delta >= 0.0f && delta < 1.0f) pi_plain = fmaf(-16.8f, delta, 1.4128f);
