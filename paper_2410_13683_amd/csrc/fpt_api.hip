@@ -3,6 +3,7 @@
 // the device kernel that evaluates the Bessel-ansatz noise table.
 #include "fpt.h"
 #include "internal.hpp"
+#include "launch_shape.hpp"
 #include "noise_node.hpp"
 #include "potential.hpp"
 
@@ -770,11 +771,7 @@ static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_tr
     block = std::min(c->opt.block_size ? c->opt.block_size : 1024, block_max);
     const int rc = occupancy_grid(fn, block, lds, c->cu_count, c->opt.blocks_per_cu, grid);
     if (rc || c->opt.block_size || c->opt.blocks_per_cu) return rc;
-    const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
-    if (waves >= (uint64_t)grid * (uint64_t)(block / 64)) return FPT_OK;
-    const uint64_t per_cu = std::min<uint64_t>((waves + cus - 1) / cus, (uint64_t)(block / 64));
-    block = 64 * (int)per_cu;
-    grid = (int)std::min<uint64_t>((uint64_t)grid, (waves + per_cu - 1) / per_cu);
+    spread_run(n_traj, c->cu_count, grid, block);
     return FPT_OK;
 }
 
@@ -791,7 +788,7 @@ static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_tr
 static int wave_pairs(const fpt_ctx *c, uint64_t n_traj, size_t lds, size_t pair_bytes)
 {
     if (c->opt.block_size || c->opt.blocks_per_cu) return 0;
-    const uint64_t waves = (n_traj + 63) / 64, cus = (uint64_t)c->cu_count;
+    const uint64_t waves = wave_count(n_traj), cus = (uint64_t)c->cu_count;
     uint64_t pairs = (waves + cus - 1) / cus;
     if (pairs > 4) pairs += pairs & 1;
     if (pairs > (uint64_t)kFeedMaxPairs || lds + pairs * pair_bytes + kFeedFlagBytes > c->lds_per_block_max) return 0;
