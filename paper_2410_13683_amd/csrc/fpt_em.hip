@@ -872,7 +872,9 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     // waves step without EVENTS first: one wave on its SIMD waits out the event's branch in every step, and
     // a wave's 64 paths end in at most 64 of its 2.5e4 groups (16,384 trajectories, slow roll -> ultra-slow
     // roll: 15.9 -> 14.4 ms here, 7.6 -> 5.0 in lanes_fp32; with four waves per SIMD they
-    // hide that wait: FP64 the same within 1 %, FP32 7 % slower for the saved state's registers).
+    // hide that wait: FP64 the same within 1 %, FP32 7 % slower for the saved state's registers).  Of paths of
+    // 35 to 2900 steps most groups are taken twice; paired, such runs are still 1.0 to 2.4 times as fast as on
+    // full blocks.
     auto group = [&](auto censor_tag, auto below_tag, auto quiet_tag, auto events_tag, const double z[4]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool BELOW = decltype(below_tag)::value;
@@ -1685,9 +1687,9 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
         2.0 * (fmax(1.4143, fabs(I.pi_in)) * dN + 2.0 * I.S_max * (fabs(a) * dN + 6.8 * sqrt_dN));
     const double phi_below = (dk.s_plus == dk.s_minus) ? __builtin_inf() : phi_T - reach;
 
-    // groups of two steps: one Philox call gives both steps' (xi_1, xi_2).  All waves step without EVENTS first
-    // (see lanes_fp64): here the saved state fits in the registers, and 3e5 trajectories went from 103.4 to
-    // 101.9 ms
+    // groups of two steps: one Philox call gives both steps' (xi_1, xi_2); without EVENTS as in lanes_fp64, in
+    // paired waves only (in all waves 3e5 paths of 1e5 steps took 101.6 instead of 103.8 ms and 1e6 the same
+    // 291, but 4e6 paths of 115 steps, most of whose groups are then taken twice, 3.9 instead of 3.4 ms)
     auto group = [&](auto censor_tag, auto below_tag, auto events_tag, const double z[4]) -> bool {
         constexpr bool CENSOR = decltype(censor_tag)::value;
         constexpr bool BELOW = decltype(below_tag)::value;
@@ -1769,10 +1771,11 @@ __device__ __forceinline__ void lanes_fp64_2d(const Inst &I, const RunArgs &R, c
     auto run_group = [&](bool may_cap, const double z[4]) {
         using Yes = std::integral_constant<bool, true>;
         using No = std::integral_constant<bool, false>;
+        using Last = std::integral_constant<bool, !FEED>;      // paired waves: without events first
         if (may_cap) group(Yes(), No(), Yes(), z);
         else if (__builtin_amdgcn_ballot_w64(live && !(phi < phi_below)) == 0) {
-            if (!group(No(), Yes(), No(), z)) group(No(), Yes(), Yes(), z);
-        } else if (!group(No(), No(), No(), z)) group(No(), No(), Yes(), z);
+            if (!group(No(), Yes(), Last(), z)) group(No(), Yes(), Yes(), z);
+        } else if (!group(No(), No(), Last(), z)) group(No(), No(), Yes(), z);
     };
 
     if constexpr (FEED) {
