@@ -443,7 +443,9 @@ int fpt_noise_table_bessel2d_time(const fpt_potential *pot, double sigma, int32_
  * afterwards with the new work list, seed and dN.  A small batch (with the default
  * block size: at most 512 trajectories per compute unit, counting each instance's
  * in whole blocks) is launched directly instead, each block on a slice of one
- * instance of its own.  The contexts must share the
+ * instance of its own, without tickets: chunk, item_size, use_graph and the tuned
+ * block size and chunk apply to the general launch only, which a given block_size
+ * always takes.  The contexts must share the
  * device and the precision; NONE and CONST biases may be mixed; MLP is not
  * supported here.  Per-trajectory outputs are not produced. */
 typedef struct fpt_batch fpt_batch;
@@ -479,11 +481,12 @@ int fpt_batch_run(fpt_batch *b, const uint64_t *n_traj, double dN, uint64_t seed
  * trajectories) beyond index 2^62 with private accumulators, keep the fastest,
  * measure each instance's mean steps per trajectory for the work order and
  * append the result to cache_path.  Contexts' histograms are not touched.
- * Synchronous.  Errors: FPT_EINVAL, FPT_EHIP. */
+ * The choice applies to the general launch (a small batch, see above, has none of
+ * these to choose).  Synchronous.  Errors: FPT_EINVAL, FPT_EHIP. */
 int fpt_batch_autotune(fpt_batch *b, const uint64_t *n_traj, double dN, uint64_t seed, const char *cache_path,
                        void *hip_stream);
 
-/* The block size and chunk the batch currently uses. */
+/* The block size and chunk that the batch's general launch currently uses. */
 int fpt_batch_config(fpt_batch *b, int32_t *block_size, int32_t *chunk);
 
 /* Duration in milliseconds of the last batch launch (HIP events on its stream; waits for it). */

@@ -1566,8 +1566,7 @@ static int batch_run_pairs(fpt_batch *b, const uint64_t *n_traj, int pairs, doub
     run.dN = dN;
     run.sqrt_dN = std::sqrt(dN);
     run.key0 = (uint32_t)seed;
-    run.key1 = (uint32_t)(seed >> 32);
-    run.chunk = b->chunk;
+    run.key1 = (uint32_t)(seed >> 32);      // (no chunk: a paired wave's lanes are never refilled)
     HIP_TRY(hipEventRecord(b->ev_start, s));
     HIP_TRY(batch_pair_launch(b->precision, b->bias_kind, b->all_pos, b->d_inst, b->d_items, run, b->max_bins,
                               b->max_tab, (int)items.size(), pairs, s));
