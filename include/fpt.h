@@ -309,8 +309,9 @@ int fpt_mlp_table(fpt_ctx *ctx, double *a_out);
  * doubles, or NULL), J_out and n_tail_out (host, or NULL; if either is given
  * the call waits for the device).  Asynchronous on hip_stream otherwise;
  * device scratch of about 36 bytes per trajectory (at most 2^22 at a time) and, up
- * to 2^19 trajectories, of the records (n0 + n1 + 64 cells per trajectory, at most
- * 256, at 18 bytes in FP32 and 34 in FP64 state) is allocated on first use and kept;
+ * to 2^19 trajectories, of the records (up to 512 cells per trajectory at 18 bytes in FP32
+ * and 34 in FP64 state, as many as 2 GiB hold but n0 + n1 + 64, at most 256, in any case) is
+ * allocated on first use and kept until fpt_destroy;
  * where there is no memory for the records, the tail is replayed.  Errors: FPT_EINVAL, FPT_ENOMEM, FPT_EHIP. */
 enum { FPT_MLP_OBJ_J = 0, FPT_MLP_OBJ_LOG_J = 1 };
 int fpt_mlp_grad(fpt_ctx *ctx, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset, double tail_lo,

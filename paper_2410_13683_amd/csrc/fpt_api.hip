@@ -1015,24 +1015,37 @@ static int mlp_grad_check(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t traj_
     return FPT_OK;
 }
 
-// Up to this many trajectories a gradient run records each path's sums per visited cell while it samples
+// Up to kRecordMax trajectories a gradient run records each path's sums per visited cell while it samples
 // (em_record_kernel) and weighs the tail's records afterwards (tail_weigh_kernel), instead of integrating
-// the tail's paths a second time: 250,000 trajectories, most of them in T, take 42 instead of 76 ms.  A
-// path makes a record per cell it leaves (57 to 59 on slow roll -> ultra-slow roll with 32 x 32 nodes);
-// the pool has room for n0 + n1 + 64 (at 18 bytes in FP32 state, 2.3 KB per trajectory there), and a
-// path that makes more is replayed.  Beyond, the pool would take gigabytes, or the sampling be cut into
-// launches that no longer fill the GPU through their ends.
+// the tail's paths a second time: 250,000 trajectories, most of them in T, take 42 instead of 76 ms, 2^19
+// take 72 (2^19 + 1, replayed, 89).  With no path in T there is nothing to save, and 250,000 take 40.8 against
+// 37.0 ms.  A path makes a record per cell it leaves: 57 to 59 on slow roll -> ultra-slow roll with 32 x 32
+// nodes, more where noise carries it over each grid line several times (48 on the exponential companion's
+// 24 x 12 nodes at dN = 2e-3, 142 at 2e-4, 130 on 64 x 16).  A path that makes more than the pool has room for is
+// replayed, and then both parts are paid for: with room for n0 + n1 + 64 alone, 250,000 of those last two took
+// 20.7 and 3.4 ms, replayed altogether 16.4 and 2.4, with the room below 8.1 and 1.6.  So the room is what
+// kRecordBytes hold (18 bytes a record in FP32 state, 34 in FP64), at most kRecordCap, at least n0 + n1 + 64 (up
+// to 256, which 2^19 trajectories in FP64 take 4.6 GB for).  What is left: with four times the companion's noise
+// (some 250 records a path, up to 800) recording and replaying costs 4 to 7 % more than replaying alone.  Beyond kRecordMax even that would not fit in
+// kRecordBytes, and the sampling cut into slices would leave the GPU idle at each slice's end.
 static const size_t kRecordMax = size_t(1) << 19;
+static const size_t kRecordBytes = size_t(1) << 31;
+static const uint64_t kRecordCap = 512;
 
-static uint32_t record_cap(const GridSpec &g) { return (uint32_t)std::min(g.n0 + g.n1 + 64, 256); }
+static uint32_t record_cap(const GridSpec &g, uint64_t n, size_t record_bytes)
+{
+    const uint64_t least = (uint64_t)std::min(g.n0 + g.n1 + 64, 256);
+    return (uint32_t)std::max(std::min<uint64_t>(kRecordBytes / (n * record_bytes), kRecordCap), least);
+}
 
 // The record pool for n trajectories in the context's memory (grown if need be, which a stream being
 // captured forbids); false if there is none.
 static bool record_pool(fpt_ctx *c, uint64_t n, hipStream_t s, RecordPool &rec)
 {
     if (n > kRecordMax) return false;
-    rec.cap = record_cap(c->grid);
-    const size_t n_rec = (size_t)n * rec.cap, sums = n_rec * (c->precision == FPT_FP64 ? 32 : 16);
+    const size_t sum_bytes = c->precision == FPT_FP64 ? 32 : 16;
+    rec.cap = record_cap(c->grid, n, sum_bytes + sizeof(uint16_t));
+    const size_t n_rec = (size_t)n * rec.cap, sums = n_rec * sum_bytes;
     const size_t bytes = sums + n_rec * sizeof(uint16_t) + (size_t)n * sizeof(uint32_t) + 64;
     if (bytes > c->rec_bytes) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
