@@ -51,75 +51,42 @@ __device__ inline double nu2_of(const Pot &p, double phi)
     return 2.25 - 3.0 * (d2V / V - r1 * r1);
 }
 
-// Background (phi, pi) and, with MODE, the mode dphi = (fr, fi) and d dphi/dN = (gr, gi).
-struct St {
-    double phi, pi_, fr, fi, gr, gi;
+// The background.
+struct Bg {
+    double phi, pi_;
 };
 
-// Time derivative in N.  Background: eq. (klein_gordon) in e-folds with H^2 = V/(3 - eps1)
-// from eq. (Friedmann).  Mode: eq. (full_delta_phi) over H^2, whose last term,
-// a^-3 d/dt(a^3 phidot^2/H), is H^2 (pi^2 (3 - eps1) + 2 pi dpi/dN).  kk = k^2.
-template <bool MODE>
-__device__ inline St deriv(const Pot &p, double kk, double N, const St &s, bool upper)
+// Its time derivative in N: eq. (klein_gordon) in e-folds with H^2 = V/(3 - eps1) from eq. (Friedmann).
+__device__ inline Bg deriv(const Pot &p, const Bg &s, bool upper)
 {
     double V, dV, d2V;
     pot_eval(p, s.phi, upper, V, dV, d2V);
     const double q = 3.0 - 0.5 * s.pi_ * s.pi_;
-    const double dpi = -q * (s.pi_ + dV / V);
-    St d;
-    d.phi = s.pi_;
-    d.pi_ = dpi;
-    if (MODE) {
-        const double inv_H2 = q / V;
-        const double m2 = (kk * exp(-2.0 * N) + d2V) * inv_H2 - s.pi_ * (s.pi_ * q + 2.0 * dpi);
-        d.fr = s.gr;
-        d.fi = s.gi;
-        d.gr = -q * s.gr - m2 * s.fr;
-        d.gi = -q * s.gi - m2 * s.fi;
-    } else {
-        d.fr = d.fi = d.gr = d.gi = 0.0;
-    }
-    return d;
+    return Bg{s.pi_, -q * (s.pi_ + dV / V)};
 }
 
-__device__ inline St axpy(const St &s, const St &k, double c)
-{
-    return St{s.phi + c * k.phi, s.pi_ + c * k.pi_, s.fr + c * k.fr, s.fi + c * k.fi, s.gr + c * k.gr,
-              s.gi + c * k.gi};
-}
+__device__ inline Bg axpy(const Bg &s, const Bg &k, double c) { return Bg{s.phi + c * k.phi, s.pi_ + c * k.pi_}; }
 
-template <bool MODE>
-__device__ inline St rk4(const Pot &p, double kk, double N, double h, const St &s, bool upper)
+__device__ inline Bg rk4(const Pot &p, double h, const Bg &s, bool upper)
 {
-    const St k1 = deriv<MODE>(p, kk, N, s, upper);
-    const St k2 = deriv<MODE>(p, kk, N + 0.5 * h, axpy(s, k1, 0.5 * h), upper);
-    const St k3 = deriv<MODE>(p, kk, N + 0.5 * h, axpy(s, k2, 0.5 * h), upper);
-    const St k4 = deriv<MODE>(p, kk, N + h, axpy(s, k3, h), upper);
+    const Bg k1 = deriv(p, s, upper);
+    const Bg k2 = deriv(p, axpy(s, k1, 0.5 * h), upper);
+    const Bg k3 = deriv(p, axpy(s, k2, 0.5 * h), upper);
+    const Bg k4 = deriv(p, axpy(s, k3, h), upper);
     const double c = h / 6.0;
-    St o;
-    o.phi = s.phi + c * (k1.phi + 2.0 * (k2.phi + k3.phi) + k4.phi);
-    o.pi_ = s.pi_ + c * (k1.pi_ + 2.0 * (k2.pi_ + k3.pi_) + k4.pi_);
-    o.fr = s.fr + c * (k1.fr + 2.0 * (k2.fr + k3.fr) + k4.fr);
-    o.fi = s.fi + c * (k1.fi + 2.0 * (k2.fi + k3.fi) + k4.fi);
-    o.gr = s.gr + c * (k1.gr + 2.0 * (k2.gr + k3.gr) + k4.gr);
-    o.gi = s.gi + c * (k1.gi + 2.0 * (k2.gi + k3.gi) + k4.gi);
-    return o;
+    return Bg{s.phi + c * (k1.phi + 2.0 * (k2.phi + k3.phi) + k4.phi),
+              s.pi_ + c * (k1.pi_ + 2.0 * (k2.pi_ + k3.pi_) + k4.pi_)};
 }
 
-// Integrate from *N to N_stop.  Steps: at most h_max and, with MODE, at most 1/800 of the
-// mode's period 2 pi aH/k.  With `kink` (piecewise-linear potential), the step that would
-// take phi from above phi_T to at or below it is cut, by bisection of its length, to end on
-// phi_T; the delta function (A_+ - A_-) delta(phi - phi_T) in V'' then adds
-// -(A_+ - A_-) dphi/(H^2 |pi|) to d dphi/dN, and phi continues one ulp below phi_T.
-template <bool MODE>
-__device__ void advance(const Pot &p, double k, double &N, double N_stop, St &s, bool kink, double h_max)
+// Integrate from *N to N_stop in steps of at most h_max.  On the piecewise-linear potential, the step that
+// would take phi from above phi_T to at or below it is cut, by bisection of its length, to end on phi_T, and
+// phi continues one ulp below phi_T.
+__device__ void advance(const Pot &p, double &N, double N_stop, Bg &s, double h_max)
 {
-    const double kk = k * k;
-    const bool has_kink = kink && p.kind == kPotPiecewiseLinear;
+    const bool has_kink = p.kind == kPotPiecewiseLinear;
     while (N < N_stop) {
-        double h = fmin(h_max, N_stop - N);
-        if (MODE) h = fmin(h, (2.0 * M_PI / kStepsPerPeriod) * exp(N) * sqrt(hubble2(p, s.phi, s.pi_)) / k);
-        const St t = rk4<MODE>(p, kk, N, h, s, false);
+        const double h = fmin(h_max, N_stop - N);
+        const Bg t = rk4(p, h, s, false);
         if (!(has_kink && s.phi > p.phi_T && t.phi <= p.phi_T)) {
             s = t;
             N += h;
@@ -128,19 +95,11 @@ __device__ void advance(const Pot &p, double k, double &N, double N_stop, St &s,
         double lo = 0.0, hi = h;
         for (int it = 0; it < 64; ++it) {
             const double mid = 0.5 * (lo + hi);
-            if (rk4<MODE>(p, kk, N, mid, s, true).phi > p.phi_T) lo = mid;
+            if (rk4(p, mid, s, true).phi > p.phi_T) lo = mid;
             else hi = mid;
         }
-        s = rk4<MODE>(p, kk, N, hi, s, true);
+        s = rk4(p, hi, s, true);
         N += hi;
-        if (MODE) {
-            double V, dV, d2V;
-            pot_eval(p, p.phi_T, true, V, dV, d2V);
-            const double H2 = V / (3.0 - 0.5 * s.pi_ * s.pi_);
-            const double kick = -(p.Ap - p.Am) / (H2 * fabs(s.pi_));
-            s.gr += kick * s.fr;
-            s.gi += kick * s.fi;
-        }
         s.phi = nextafter(p.phi_T, -INFINITY);
     }
 }
@@ -170,10 +129,6 @@ __device__ inline void bessel_j(double mu, double y, double &J, double &yJp)
 // held as differences from the step's start, so that the extrapolation's weights (up to 50) do not
 // multiply the rounding of the state itself.
 // ---------------------------------------------------------------------------
-struct Bg {
-    double phi, pi_;
-};
-
 // 1/x for normal x, to about an ulp: the hardware reciprocal and two Newton steps.
 __device__ __forceinline__ double recip(double x)
 {
@@ -333,9 +288,7 @@ __global__ void __launch_bounds__(64) bg_macro_kernel(Pot pot, double phi_start,
             ++nrec;
             N += (double)m * kBgStep;
         } else {
-            St s{y.phi, y.pi_, 0.0, 0.0, 0.0, 0.0};
-            advance<false>(p, 0.0, N, N + kBgStep, s, true, kBgStep);
-            z = Bg{s.phi, s.pi_};
+            advance(p, N, N + kBgStep, z, kBgStep);
         }
         i += m;
         y = z;
@@ -375,8 +328,7 @@ __global__ void __launch_bounds__(256) bg_fill_kernel(Pot p, BgStore b)
         }
         if (have || i == r.first + 1) {
             if (!have) y = Bg{r.phi, r.pi_};
-            const St s = rk4<false>(p, 0.0, 0.0, kBgStep, St{y.phi, y.pi_, 0.0, 0.0, 0.0, 0.0}, r.upper != 0);
-            y = Bg{s.phi, s.pi_};
+            y = rk4(p, kBgStep, y, r.upper != 0);
         } else {
             y = extrapolated(p, Bg{r.phi, r.pi_}, (double)(i - r.first) * kBgStep, r.upper != 0);
         }
@@ -428,7 +380,7 @@ __device__ inline bool bd_node(const Pot &p, double sigma, double phi, double &S
 // ---------------------------------------------------------------------------
 // Modes.  The mode that crosses k = sigma a H at N_sigma starts at the last sample with k >= 100 aH
 // and is solved to N_sigma in P segments whose ends are samples: equal shares of the RK4 steps that
-// the step rule of advance asks for, with y = k/(aH) falling as e^-N from 100.
+// the step rule of mode_segment_kernel asks for, with y = k/(aH) falling as e^-N from 100.
 // ---------------------------------------------------------------------------
 // One node's mode: status 0 none (no matching), else start sample i0 and end time Ns.
 struct ModeJob {
@@ -494,8 +446,20 @@ __device__ inline int segment_start(const Pot &p, const ModeJob &q, const BgStor
     return (i > b.end->last || !(b.N[min(i, b.end->last)] < q.Ns)) ? INT_MAX : i;
 }
 
-// The time derivative of background and mode with E = k^2 e^(-2N) given: deriv<true> with one
-// reciprocal in place of its divisions.  w = q/V = 1/H^2.
+// Background (phi, pi), the mode dphi = (fr, fi) and d dphi/dN = (gr, gi).
+struct St {
+    double phi, pi_, fr, fi, gr, gi;
+};
+
+__device__ inline St axpy(const St &s, const St &k, double c)
+{
+    return St{s.phi + c * k.phi, s.pi_ + c * k.pi_, s.fr + c * k.fr, s.fi + c * k.fi, s.gr + c * k.gr,
+              s.gi + c * k.gi};
+}
+
+// The time derivative of background and mode with E = k^2 e^(-2N) given: deriv's, and eq. (full_delta_phi) over
+// H^2, whose last term, a^-3 d/dt(a^3 phidot^2/H), is H^2 (pi^2 (3 - eps1) + 2 pi dpi/dN), with one reciprocal in
+// place of the divisions.  w = q/V = 1/H^2.
 __device__ __forceinline__ St mode_deriv(const Pot &p, double E, const St &s, bool upper, double &w)
 {
     double V, dV, d2V;
@@ -525,8 +489,12 @@ __device__ __forceinline__ St mode_rk4(const Pot &p, double E1, double E2, doubl
 }
 
 // The propagator of one segment of one mode: the solutions that start as (f, g) = (1, 0) and (0, 1),
-// carried as the real and imaginary parts of one state, with the step rule and the kink of advance.
-// E = k^2 e^(-2N) is carried along by the series of e^(-h) (h <= 2.5e-4: h^5/120 < 1e-20).
+// carried as the real and imaginary parts of one state.  RK4 steps of at most kModeMaxStep and at most 1/800
+// of the mode's period 2 pi aH/k; the step that takes phi over the kink of the piecewise-linear potential ends
+// on it, where the delta function (A_+ - A_-) delta(phi - phi_T) in V'' adds -(A_+ - A_-) dphi/(H^2 |pi|) to
+// d dphi/dN, and phi continues one ulp below phi_T.
+// E = k^2 e^(-2N) is carried along by the series of e^(-x) (at the step's middle x = h, at its end x = 2 h <=
+// 5e-4: x^5/120 < 3e-19).
 // Node j, segment s is thread s n + j, so that a wave's lanes hold neighbouring nodes in the same
 // segment and step alike.
 // One thread per mode left 64 waves on the chip, each a chain of 2.3e4 steps: 25.0 ms for 4096 nodes.
@@ -572,10 +540,10 @@ __global__ void __launch_bounds__(256) mode_segment_kernel(Pot pot, int n, int P
             // nearly straight over 2.5e-4 e-folds, so four steps reach the rounding; the lanes of a wave
             // cross at steps of their own, so this part runs once per lane and a bisection's 256
             // evaluations there took three quarters of the kernel)
-            const St s0{s.phi, s.pi_, 0.0, 0.0, 0.0, 0.0};
+            const Bg s0{s.phi, s.pi_};
             double hi = h * (s.phi - p.phi_T) / (s.phi - u.phi);
             for (int it = 0; it < 4; ++it) {
-                const St v = rk4<false>(p, 0.0, N, hi, s0, true);
+                const Bg v = rk4(p, hi, s0, true);
                 hi = fmin(fmax(hi - (v.phi - p.phi_T) / v.pi_, 0.0), h);
             }
             e1 = decay(hi);
