@@ -783,8 +783,10 @@ static int run_shape(const fpt_ctx *c, const void *fn, size_t lds, uint64_t n_tr
 // against 30.2 ms, 1e4 of the linear problem 0.79 against 1.28 ms; with 2D noise 32,768 take 19.6 against 36.9
 // ms in FP64 and 8.6 against 13.3 in FP32 state, 65,536 26.5 against 34.4 and 10.9 against 13.2.  Beyond, four
 // integrating waves per SIMD keep it busy by themselves, and with 2D noise a table of 2048 nodes leaves no
-// LDS for eight pairs.  Odd counts above 4 are rounded up: seven pairs took longer than eight (12.1 against
-// 10.7 ms).
+// LDS for eight pairs.  (The 2D figures are of phi tables; the FP32 state on a 2D time table has no paired kernel.)
+// Paths of 35 to 2900 steps gain as well: 1000 trajectories take 0.43 to 0.87 of the time on full blocks, 131,072 0.42
+// to 1.03, the most where they end together.  Odd counts above 4 are rounded up: seven pairs took longer than
+// eight (12.1 against 10.7 ms).
 static int wave_pairs(const fpt_ctx *c, uint64_t n_traj, size_t lds, size_t pair_bytes)
 {
     if (c->opt.block_size || c->opt.blocks_per_cu) return 0;

@@ -851,7 +851,7 @@ __device__ __forceinline__ void lanes_fp64(const Inst &I, const RunArgs &R, cons
     // starts the group further below phi_T than that, the drift takes the lower branch's constant without a
     // comparison and two selects per step.  With the event's masks and the table index this took 1e6
     // slow-roll -> ultra-slow-roll trajectories from 193.8 to 183.6 ms, with a constant bias from 227 to 199
-    // ms (109 and 128 VGPRs to 97 and 117).  Keeping the lane's table record in registers between steps,
+    // ms (109 and 128 VGPRs to 95 and 113).  Keeping the lane's table record in registers between steps,
     // tried instead of the lookup, was slower (198 ms): its check is a branch in every step.
     constexpr bool CAN_BELOW = POT == kPotPiecewiseLinear && !LEARNED;
     const double reach = 4.0 * (fmax(1.4143, fabs(I.pi_in)) * dN + I.S_max * (fabs(a_const) * dN + 6.8 * sqrt_dN));
@@ -2516,11 +2516,18 @@ const void *kptr() { return reinterpret_cast<const void *>(&em_kernel<PREC, BIAS
 template <int PREC, int BIAS, bool ALLPOS>
 const void *bptr() { return reinterpret_cast<const void *>(&batch_kernel<PREC, BIAS, ALLPOS>); }
 
+// (none for a learned control on a time table, which fpt_create refuses)
 template <int PREC, int BIAS>
 struct KTab {
+    template <bool ALLPOS>
+    static const void *on_time()
+    {
+        if constexpr (BIAS == kBiasNone || BIAS == kBiasConst) return kptr<PREC, BIAS, 2, ALLPOS>();
+        else return nullptr;
+    }
     const void *p[3][2] = {{kptr<PREC, BIAS, 0, false>(), kptr<PREC, BIAS, 0, true>()},
                            {kptr<PREC, BIAS, 1, false>(), kptr<PREC, BIAS, 1, true>()},
-                           {kptr<PREC, BIAS, 2, false>(), kptr<PREC, BIAS, 2, true>()}};
+                           {on_time<false>(), on_time<true>()}};
 };
 
 }  // namespace
