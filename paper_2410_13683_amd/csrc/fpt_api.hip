@@ -18,6 +18,7 @@
 #include <vector>
 #include <limits>
 #include <mutex>
+#include <numeric>
 #include <initializer_list>
 #include <memory>
 #include <new>
@@ -731,7 +732,8 @@ extern "C" int fpt_create(const fpt_potential *pot, const fpt_noise_table *table
     }
     const int n_cells = grid_cells(I);
     size_t need = dim == 2 ? em2d_lds_bytes(o.n_bins, nt, o.precision)
-                           : em_lds_bytes(o.n_bins, nt, o.precision, n_cells, b.kind == FPT_BIAS_MLP && b.mlp_every > 0);
+                           : em_lds_bytes(o.n_bins, nt, o.precision, n_cells,
+                                          b.kind == FPT_BIAS_MLP && b.mlp_every > 0 ? kBiasMlpExact : b.kind);
     if (b.kind == FPT_BIAS_MLP)
         need = std::max(need, replay_lds_bytes(nt, o.precision, n_cells, c->grid.n0 * c->grid.n1));
     if (need > c->lds_per_block_max) {
@@ -797,6 +799,28 @@ static int wave_pairs(const fpt_ctx *c, uint64_t n_traj, size_t lds, size_t pair
     return (int)pairs;
 }
 
+// Whether a run of the FP32 network takes the matrix cores (two waves per SIMD) or scalar weights (four).  Up to
+// two waves per SIMD the matrix cores are the faster at every interval (1.1 to 3 times, k = 1024 to 8).  Beyond,
+// the cost of a step on a full GPU is 92 + 4698/e on them and 47 + 6618/e on scalar weights (ms for 2e6
+// trajectories of 2.5e4 steps, from k = 64 and 128; k = 32 is met within 4 %), where e is the interval
+// at which a wave evaluates: k while its lanes all started together, and the common divisor of k and the chunk once
+// lanes are refilled, at chunk ends, which leaves them at other phases of k.  (262,144 trajectories at k = 48: 30
+// ms on scalar weights, which hold them all at once, 38 on the matrix cores; 400,000: 85 and 71.)  Up to three
+// full grids of scalar waves, whose last one is partly empty, these have to be 15 % ahead: at k = 64, 262,144
+// to 600,000 trajectories take 24.5 to 54.8 against 22.6 to 53.6 ms, 1e6 79 against 83, 1e7 (slow roll ->
+// ultra-slow roll) 2924 against 3276.
+static bool network_on_matrix(const fpt_ctx *c, uint64_t n_traj)
+{
+    if (c->precision != FPT_FP32_STATE ||
+        em_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision, 0, kBiasMlpMatrix) > c->lds_per_block_max)
+        return false;
+    const uint64_t two_waves = (uint64_t)c->cu_count * kMaxBlockMatrix;
+    if (n_traj <= two_waves) return true;
+    const double every = c->inst.mlp_every, refilled = std::gcd(c->inst.mlp_every, c->opt.chunk ? c->opt.chunk : 128);
+    const double matrix = 92.0 + 4698.0 / refilled, scalar = 47.0 + 6618.0 / (n_traj <= 2 * two_waves ? every : refilled);
+    return matrix < scalar * (n_traj < 6 * two_waves ? 1.15 : 1.0);
+}
+
 extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset,
                        void *hip_stream, double *d_N, double *d_lnw, uint32_t *d_steps)
 {
@@ -825,15 +849,15 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     const bool two_d = c->inst.noise_dim == 2;
     // the learned control runs its tabulated network, or the network itself every mlp_every steps
     const bool exact = c->inst.bias_kind == kBiasMlp && c->inst.mlp_every > 0;
-    const int bias_k = exact ? kBiasMlpExact : c->inst.bias_kind;
+    const int bias_k = !exact ? c->inst.bias_kind : network_on_matrix(c, n_traj) ? kBiasMlpMatrix : kBiasMlpExact;
     const void *fn = two_d ? em2d_kernel_ptr(c->precision, c->inst.bias_kind, c->inst.all_S_pos != 0,
                                              tab_mode(c->inst) == 2)
                            : em_kernel_ptr(c->precision, bias_k, tab_mode(c->inst), c->inst.all_S_pos != 0,
                                            c->inst.pot_kind);
     const size_t lds = two_d ? em2d_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision)
                              : em_lds_bytes(c->inst.hist.n_bins, c->inst.n_tab, c->precision, grid_cells(c->inst),
-                                            exact);
-    const int rc = run_shape(c, fn, lds, n_traj, grid, block, exact && c->precision == FPT_FP32_STATE ? kMaxBlockNet32 : 1024);
+                                            bias_k);
+    const int rc = run_shape(c, fn, lds, n_traj, grid, block, bias_k == kBiasMlpMatrix ? kMaxBlockMatrix : 1024);
     if (rc) return rc;
     const void *pair_fn = nullptr;
     const size_t pair_bytes = (two_d ? 2 : 1) * kFeedBytes;
@@ -858,7 +882,7 @@ extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, ui
     HIP_TRY(zero_words(p.cursor, 1, s));
     HIP_TRY(hipEventRecord(c->ev_start, s));
     if (two_d) HIP_TRY(em2d_launch(p, c->precision, grid, block, s));
-    else HIP_TRY(em_launch(p, c->precision, grid, block, s, exact));
+    else HIP_TRY(em_launch(p, c->precision, bias_k, grid, block, s));
     HIP_TRY(hipEventRecord(c->ev_stop, s));
     HIP_TRY(hipEventRecord(c->ev_done, s));
     c->ran = true;
@@ -1146,7 +1170,7 @@ static int mlp_grad_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, u
             HIP_TRY(tail_weigh(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, *rec, c->precision,
                                g.n0, g.n1, c->d_G, d_tail, &cnt[0], &cnt[1], c->d_J, c->cu_count, s));
         } else {
-            HIP_TRY(em_launch(p, c->precision, grid_em, block_em, s));
+            HIP_TRY(em_launch(p, c->precision, kBiasMlp, grid_em, block_em, s));
             HIP_TRY(mlp_tail_compact(d_N, d_lnw, d_steps, m, traj_offset + done, c->opt.N_ref, tail_lo, d_tail,
                                      &cnt[0], &cnt[1], c->d_J, s));
         }

@@ -600,7 +600,7 @@ __device__ __forceinline__ void grad_add(T s[4], T c, T f0, T f1)
 // at a time, each pass recomputing the 64 first-layer activations, so that a lane holds eight
 // accumulators instead of 64 activations.
 //
-// FP32 state: the second layer, 64 x 64 for the wave's 64 states, runs on the matrix cores as 128
+// FP32 state, kBiasMlpMatrix: the second layer, 64 x 64 for the wave's 64 states, runs on the matrix cores as 128
 // v_mfma_f32_32x32x1 (two blocks of 32 states, one input unit per instruction).  Such an instruction is
 // one fused multiply-add per element, rounded like v_fma_f32 (bit for bit over 8e5 elements of mixed
 // scales), so the sums are those of a chain of multiply-adds in the order of the input units, two
@@ -609,10 +609,16 @@ __device__ __forceinline__ void grad_add(T s[4], T c, T f0, T f1)
 // instructions; W1, b1 and W3 are read in place through the constant address space (scalar loads).
 // Bound: the 128 instructions take 9.6e3 cycles an evaluation (75 each measured) and the FP32 vector
 // work, which does not run beside FP32 matrix instructions, some 5e3 more (256 exp2 and reciprocals at
-// 8 cycles among it); 1.6e4 measured.  The 128 accumulators leave two waves per SIMD.  Before, the 4096
-// multiply-adds took the weights as scalar operands, 17.9 KB through the 16 KB scalar cache, whose
-// waits left 2e4 to 5.6e4 cycles an evaluation: 1e5 trajectories at k = 16 went from 238 to 104 ms,
-// 1000 trajectories (one wave per SIMD) from 147 to 67 ms.
+// 8 cycles among it); 1.6e4 measured.  The 128 accumulators leave two waves per SIMD.
+//
+// FP32 state, kBiasMlpExact: the parameters are read in place through the constant address space.  Every
+// lane of a wave reads the same word, so the loads are scalar and the 4096 multiply-adds take the weights as
+// scalar operands; a lane keeps its 64 first-layer activations in registers, and four waves per SIMD fit.
+// The 17.9 KB pass through the 16 KB scalar cache, whose waits leave 2e4 to 5.6e4 cycles an evaluation: 1e5
+// trajectories at k = 16 take 238 ms against 104 on the matrix cores, 1000 (one wave per SIMD) 147 and 67.
+// Between evaluations four waves hide more than two: 2e6 trajectories (of 2.5e4 steps) at k = 128 take 98.5 ms
+// against 128, at k = 1024 84 against 120.  fpt_run chooses by the estimate of network_on_matrix.  Both add
+// in the same order, bit for bit.
 // tanh s = 1 - 2/(e^(2s) + 1) from the hardware exp2 and reciprocal, exactly +-1 for large |s|.
 // ---------------------------------------------------------------------------
 constexpr int kMlpChunk = 8;
@@ -685,6 +691,28 @@ __device__ __forceinline__ float mlp_tanh32(float s)
 {
     const float e = __builtin_amdgcn_exp2f(s * 2.8853900817779268f);   // e^(2s) = 2^(2 s log2 e)
     return fmaf(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
+}
+
+__device__ __forceinline__ float mlp_out0_32_scalar(const_float *p, float x0, float x1)
+{
+    constexpr int H = kMlpHidden;
+    float h[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j)
+        h[j] = mlp_tanh32(fmaf(p[kOffW1 + 2 * j], x0, fmaf(p[kOffW1 + 2 * j + 1], x1, p[kOffB1 + j])));
+    float out = p[kOffB3];
+    for (int o = 0; o < H; ++o) {
+        const_float *row = p + kOffW2 + o * H;
+        // two partial sums: two independent chains of multiply-adds
+        float s0 = p[kOffB2 + o], s1 = 0.0f;
+#pragma unroll
+        for (int j = 0; j < H; j += 2) {
+            s0 = fmaf(row[j], h[j], s0);
+            s1 = fmaf(row[j + 1], h[j + 1], s1);
+        }
+        out = fmaf(p[kOffW3 + o], mlp_tanh32(s0 + s1), out);
+    }
+    return out;
 }
 
 // Every lane of the wave must take part (the weights of output unit lane % 32 come from each lane).
@@ -1182,11 +1210,12 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
                                            uint64_t n_traj, uint64_t traj_offset, const Feed &feed = Feed{})
 {
     static_assert(!GRAD || BIAS == kBiasMlp, "gradients need the tabulated control");
-    constexpr bool LEARNED = BIAS == kBiasMlp || BIAS == kBiasMlpExact;
+    constexpr bool EXACT = BIAS == kBiasMlpExact || BIAS == kBiasMlpMatrix;
+    constexpr bool LEARNED = BIAS == kBiasMlp || EXACT;
     // steps per group: 16 (four generator calls), so that the group's fixed work (table record,
     // renormalisation, FP64 sums, loop control) is shared by 16 steps; the normals of the whole
     // group are formed first.  The exact network keeps groups of 4 and one copy of its code.
-    constexpr int G = (BIAS == kBiasMlpExact) ? 4 : 16;
+    constexpr int G = EXACT ? 4 : 16;
     const_float *wp = (const_float *)(uintptr_t)I.mlp_params;
     const NetConsts32 nq = net_consts32(I);
     const uint32_t every = (uint32_t)I.mlp_every;
@@ -1322,7 +1351,7 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             if (LEARNED) return lnw - (double)zacc;
             return lnw_of(zsum + (double)zacc, ALLPOS ? steps : PLAIN ? n_on + (steps - n) : n_on);
         };
-#pragma unroll(BIAS == kBiasMlpExact ? 1 : G)   // the exact network: one copy of its code
+#pragma unroll(EXACT ? 1 : G)   // the exact network: one copy of its code
         for (int j = 0; j < G; ++j) {
             const float zj = (G == 4) ? pick4(z, j) : z[j];
             if (CENSOR && live && n + j == I.max_steps) {
@@ -1388,6 +1417,14 @@ __device__ __forceinline__ void lanes_fp32(const Inst &I, const RunArgs &R, cons
             float f0 = 0.0f, f1 = 0.0f;
             if (BIAS == kBiasMlp) a = grid_amp32(gc, l_grid, xs, ps, cell, f0, f1);
             if (BIAS == kBiasMlpExact) {
+                if (n + j == next_eval) {
+                    a_held = mlp_out0_32_scalar(wp, fmaf(xs, nq.k0, nq.off0),
+                                                fmaf(__builtin_amdgcn_logf(fmaxf(fabsf(ps), 1e-30f)), nq.k1, nq.off1));
+                    next_eval += every;
+                }
+                a = a_held;
+            }
+            if (BIAS == kBiasMlpMatrix) {
                 const bool due = n + j == next_eval;
                 if (__any(due)) {      // by the whole wave; lanes at other phases keep what they hold
                     const float v = mlp_out0_32(wp, reinterpret_cast<const float *>(l_grid), fmaf(xs, nq.k0, nq.off0),
@@ -2143,7 +2180,7 @@ __device__ __forceinline__ RetireTo retire_to(const EmParams &p, const LdsAcc &a
 }
 
 template <int PREC, int BIAS, int TAB, bool ALLPOS, int POT = kPotPiecewiseLinear>
-__global__ void __launch_bounds__(BIAS == kBiasMlpExact && PREC == 1 ? kMaxBlockNet32 : 1024) FPT_EM_OCCUPANCY
+__global__ void __launch_bounds__(BIAS == kBiasMlpMatrix ? kMaxBlockMatrix : 1024) FPT_EM_OCCUPANCY
 em_kernel(EmParams p)
 {
     static_assert(POT == kPotPiecewiseLinear || (PREC == 0 && (BIAS == kBiasNone || BIAS == kBiasConst)),
@@ -2157,7 +2194,7 @@ em_kernel(EmParams p)
     else stage_table32(p.inst, reinterpret_cast<float4 *>(l_tab), (float)p.run.dN);
     if (BIAS == kBiasMlp) stage_grid<PREC>(p.inst, l_grid);
     if (BIAS == kBiasMlpExact && PREC == 0) stage_mlp64(p.inst.mlp_params, reinterpret_cast<double *>(l_grid));
-    if (BIAS == kBiasMlpExact && PREC == 1) stage_mlp32(p.inst.mlp_params, reinterpret_cast<float *>(l_grid));
+    if (BIAS == kBiasMlpMatrix) stage_mlp32(p.inst.mlp_params, reinterpret_cast<float *>(l_grid));
     __syncthreads();
     const RetireTo rt = retire_to(p, acc);
     const ReplayTo rp{nullptr, nullptr, nullptr};
@@ -2532,10 +2569,13 @@ struct KTab {
 
 }  // namespace
 
-size_t em_lds_bytes(int n_bins, int n_tab, int precision, int n_cells, bool mlp_exact)
+size_t em_lds_bytes(int n_bins, int n_tab, int precision, int n_cells, int bias_kind)
 {
-    // the exact network stages its parameters instead of the tabulated cells
-    const size_t bias = mlp_exact ? (precision == 0 ? kMlpLdsBytes64 : kMlpLdsBytes32) : cell_bytes(precision, n_cells);
+    // the exact network stages its parameters (FP64), its second layer's (matrix cores) or nothing instead of the
+    // tabulated cells
+    const size_t bias = bias_kind == kBiasMlpMatrix  ? kMlpLdsBytes32
+                        : bias_kind == kBiasMlpExact ? (precision == 0 ? kMlpLdsBytes64 : 0)
+                                                     : cell_bytes(precision, n_cells);
     return align16(acc_bytes(n_bins)) + tab_bytes(precision, n_tab) + bias;
 }
 
@@ -2567,11 +2607,13 @@ const void *em_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_p
     static const KTab<1, kBiasConst> f1c;
     static const KTab<1, kBiasMlp> f1m;
     static const KTab<1, kBiasMlpExact> f1x;
+    static const KTab<1, kBiasMlpMatrix> f1m32;
     const void *const(*t)[2];
     if (precision == 0)
         t = bias_kind == kBiasNone ? f0n.p : bias_kind == kBiasConst ? f0c.p : bias_kind == kBiasMlp ? f0m.p : f0x.p;
     else
-        t = bias_kind == kBiasNone ? f1n.p : bias_kind == kBiasConst ? f1c.p : bias_kind == kBiasMlp ? f1m.p : f1x.p;
+        t = bias_kind == kBiasNone ? f1n.p : bias_kind == kBiasConst ? f1c.p : bias_kind == kBiasMlp ? f1m.p
+            : bias_kind == kBiasMlpExact ? f1x.p : f1m32.p;
     return t[tm][all_pos ? 1 : 0];
 }
 
@@ -2598,10 +2640,10 @@ const void *em_pair_kernel_ptr(int precision, int bias_kind, int tab_mode, bool 
     return t[tab_mode][all_pos ? 1 : 0];
 }
 
-hipError_t em_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream, bool mlp_exact)
+hipError_t em_launch(const EmParams &p, int precision, int bias_kind, int grid, int block, hipStream_t stream)
 {
-    const size_t lds = em_lds_bytes(p.inst.hist.n_bins, p.inst.n_tab, precision, grid_cells(p.inst), mlp_exact);
-    const void *fn = em_kernel_ptr(precision, mlp_exact ? kBiasMlpExact : p.inst.bias_kind, tab_mode(p.inst),
+    const size_t lds = em_lds_bytes(p.inst.hist.n_bins, p.inst.n_tab, precision, grid_cells(p.inst), bias_kind);
+    const void *fn = em_kernel_ptr(precision, bias_kind, tab_mode(p.inst),
                                    p.inst.all_S_pos != 0, p.inst.pot_kind);
     EmParams pp = p;
     void *args[] = {&pp};

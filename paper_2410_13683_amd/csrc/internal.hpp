@@ -12,10 +12,10 @@ namespace fpt {
 
 enum : int { kPotPiecewiseLinear = 0, kPotExponential = 1, kPotGaussianBump = 2 };
 enum : int { kBiasNone = 0, kBiasConst = 1, kBiasMlp = 2 };
-// kernel-side bias variant (not in the ABI): the learned control's network evaluated exactly every
-// mlp_every steps instead of read from its table
-constexpr int kBiasMlpExact = 3;
-constexpr int kMaxBlockNet32 = 512;   // largest block of its FP32 kernel (two waves per SIMD)
+// kernel-side bias variants (not in the ABI): the learned control's network evaluated exactly every
+// mlp_every steps instead of read from its table; kBiasMlpMatrix on the matrix cores (FP32 state)
+constexpr int kBiasMlpExact = 3, kBiasMlpMatrix = 4;
+constexpr int kMaxBlockMatrix = 512;   // largest block of the latter (two waves per SIMD)
 enum : int { kBinsLinear = 0, kBinsLog = 1 };
 
 constexpr uint32_t kFlagCensored = 0x80000000u;
@@ -159,13 +159,13 @@ struct ReplayParams {
 
 // Euler-Maruyama kernels (fpt_em.hip).
 __host__ __device__ inline int grid_cells(const Inst &I) { return I.bias_kind == kBiasMlp ? (I.g_n0 - 1) * (I.g_n1 - 1) : 0; }
-size_t em_lds_bytes(int n_bins, int n_tab, int precision, int n_cells, bool mlp_exact = false);
+// bias_kind: kBiasMlpExact or kBiasMlpMatrix for the network itself, any other reads n_cells control cells
+size_t em_lds_bytes(int n_bins, int n_tab, int precision, int n_cells, int bias_kind = kBiasNone);
 size_t replay_lds_bytes(int n_tab, int precision, int n_cells, int n_nodes);
 // tab_mode: 0 a single node, 1 nodes in phi, 2 nodes in time (tab_mode(inst)); pot_kind selects
 // the Gaussian-bump variant (FP64, bias none or constant only).
 const void *em_kernel_ptr(int precision, int bias_kind, int tab_mode, bool all_pos, int pot_kind = 0);
-hipError_t em_launch(const EmParams &p, int precision, int grid, int block, hipStream_t stream,
-                     bool mlp_exact = false);
+hipError_t em_launch(const EmParams &p, int precision, int bias_kind, int grid, int block, hipStream_t stream);
 // The paired-wave variant for runs of at most 64 kFeedMaxPairs trajectories per CU (bias none or
 // constant; nullptr otherwise): blocks of up to kFeedMaxPairs pairs of waves, kFeedBytes of
 // LDS per pair after em_lds_bytes (2D noise: em2d_pair_kernel, twice that).  kFeedSteps (FP64) or kFeedSteps32 steps' normals are handed over at a time.
