@@ -801,14 +801,17 @@ static int wave_pairs(const fpt_ctx *c, uint64_t n_traj, size_t lds, size_t pair
 
 // Whether a run of the FP32 network takes the matrix cores (two waves per SIMD) or scalar weights (four).  Up to
 // two waves per SIMD the matrix cores are the faster at every interval (1.1 to 3 times, k = 1024 to 8).  Beyond,
-// the cost of a step on a full GPU is 92 + 4698/e on them and 47 + 6618/e on scalar weights (ms for 2e6
-// trajectories of 2.5e4 steps, from k = 64 and 128; k = 32 is met within 4 %), where e is the interval
-// at which a wave evaluates: k while its lanes all started together, and the common divisor of k and the chunk once
-// lanes are refilled, at chunk ends, which leaves them at other phases of k.  (262,144 trajectories at k = 48: 30
-// ms on scalar weights, which hold them all at once, 38 on the matrix cores; 400,000: 85 and 71.)  Up to three
-// full grids of scalar waves, whose last one is partly empty, these have to be 15 % ahead: at k = 64, 262,144
-// to 600,000 trajectories take 24.5 to 54.8 against 22.6 to 53.6 ms, 1e6 79 against 83, 1e7 (slow roll ->
-// ultra-slow roll) 2924 against 3276.
+// the cost of a step on a full GPU is 92 + 4698 x on them and 47 + 6618 x on scalar weights (ms for 2e6
+// trajectories of 2.5e4 steps, from k = 64 and 128; k = 32 is met within 4 %), where x is how often a wave
+// evaluates, per step: 1/k while its lanes all started together, more once lanes are refilled, at chunk ends that
+// k does not divide, which leaves them at other phases of k.  (262,144 trajectories at k = 48: 30 ms on scalar
+// weights, which hold them all at once, 38 on the matrix cores; 400,000: 85 and 71.)  How many phases there are
+// depends on the paths; two are taken, so that the matrix cores are chosen only where they gain in any case: where
+// paths end close together k = 1000 has few of its 125 phases (1e6 trajectories 6.0 against 9.2 ms), and where
+// there are many the matrix cores would gain (k = 100, paths of widely spread lengths: 172 and 131 ms).  Where k
+// divides the chunk, up to three full grids of scalar waves, whose last one is partly empty, these have to be 15 %
+// ahead: at k = 64, 262,144 to 600,000 trajectories take 24.5 to 54.8 against 22.6 to 53.6 ms, 1e6 79 against 83,
+// 1e7 (slow roll -> ultra-slow roll) 2924 against 3276.
 static bool network_on_matrix(const fpt_ctx *c, uint64_t n_traj)
 {
     if (c->precision != FPT_FP32_STATE ||
@@ -816,9 +819,15 @@ static bool network_on_matrix(const fpt_ctx *c, uint64_t n_traj)
         return false;
     const uint64_t two_waves = (uint64_t)c->cu_count * kMaxBlockMatrix;
     if (n_traj <= two_waves) return true;
-    const double every = c->inst.mlp_every, refilled = std::gcd(c->inst.mlp_every, c->opt.chunk ? c->opt.chunk : 128);
-    const double matrix = 92.0 + 4698.0 / refilled, scalar = 47.0 + 6618.0 / (n_traj <= 2 * two_waves ? every : refilled);
-    return matrix < scalar * (n_traj < 6 * two_waves ? 1.15 : 1.0);
+    const int k = c->inst.mlp_every, chunk = c->opt.chunk ? c->opt.chunk : 128;
+    const double first = 1.0 / k, refilled = 1.0 / std::max((double)std::gcd(k, chunk), 0.5 * k);
+    auto per_step = [&](double lanes) {      // the first `lanes` trajectories start together
+        const double together = std::min(1.0, lanes / (double)n_traj);
+        return together * first + (1.0 - together) * refilled;
+    };
+    const double matrix = 92.0 + 4698.0 * per_step((double)two_waves);
+    const double scalar = 47.0 + 6618.0 * per_step(2.0 * (double)two_waves);
+    return matrix < scalar * (chunk % k == 0 && n_traj < 6 * two_waves ? 1.15 : 1.0);
 }
 
 extern "C" int fpt_run(fpt_ctx *c, uint64_t n_traj, double dN, uint64_t seed, uint64_t traj_offset,
