@@ -92,9 +92,9 @@ PEAK_HBM_GBS = 8000.0
 # process (FETCH_SIZE reads 0.5 GiB: x2.0; WRITE_SIZE reads 1 GiB: x1.0).  Valid only for the
 # kernel source it was measured on (hash of the kernel file and its header).
 MEASURED_TRAFFIC = {
-    "source_sha256": "0bca8a505e2c731396a9a69d5a1d2477a2c416b93f81a96f1921b89c18680690",
+    "source_sha256": "17f5a3b4d9903985d859c8b234cb8aebd035e8c2ecc5b2729a27cab0f2fa0bca",
     "workload": "srusr_is_fp32_A2", "n_traj": 100_000_000,
-    "fetch_bytes": 10931.4375 * 1024 * 2.0, "write_bytes": 2127300.90625 * 1024 * 1.0,
+    "fetch_bytes": 10937.25 * 1024 * 2.0, "write_bytes": 2127443.6875 * 1024 * 1.0,
 }
 
 
@@ -143,16 +143,16 @@ def kernel_source_sha() -> str:
 # 2 FMA + ADD + MUL + TRANS of each precision.  They measure what the compiled kernel executes,
 # beside the operation-by-operation count of the method used for "achieved".
 MEASURED_VALU = {
-    "source_sha256": "0bca8a505e2c731396a9a69d5a1d2477a2c416b93f81a96f1921b89c18680690",
-    "srusr_is_fp32_A2": {"VALUBusy": 139.173, "VALUUtilization": 98.989,
-                         "hw_flops_per_step": {"f32": 27.720, "f64": 0.143},
+    "source_sha256": "17f5a3b4d9903985d859c8b234cb8aebd035e8c2ecc5b2729a27cab0f2fa0bca",
+    "srusr_is_fp32_A2": {"VALUBusy": 138.793, "VALUUtilization": 98.989,
+                         "hw_flops_per_step": {"f32": 27.719, "f64": 0.143},
                          "insts_per_step": {"FMA_F32": 10.351, "ADD_F32": 3.325, "MUL_F32": 1.689,
                                             "TRANS_F32": 2.003, "CVT": 1.263, "INT32": 0.625,
                                             "FMA_F64": 0.025, "ADD_F64": 0.094}},
-    "srusr_bessel_fp64": {"VALUBusy": 93.582, "VALUUtilization": 99.732,
-                          "hw_flops_per_step": {"f32": 0.0, "f64": 57.052},
-                          "insts_per_step": {"FMA_F64": 19.942, "ADD_F64": 5.304, "MUL_F64": 10.350,
-                                             "TRANS_F64": 1.515, "INT32": 4.928, "FMA_F32": 0.0,
+    "srusr_bessel_fp64": {"VALUBusy": 93.769, "VALUUtilization": 99.732,
+                          "hw_flops_per_step": {"f32": 0.0, "f64": 57.102},
+                          "insts_per_step": {"FMA_F64": 19.959, "ADD_F64": 5.308, "MUL_F64": 10.359,
+                                             "TRANS_F64": 1.516, "INT32": 4.932, "FMA_F32": 0.0,
                                              "ADD_F32": 0.0, "MUL_F32": 0.0}},
 }
 # the issue rate of independent v_fma_f32 chains, wave-instructions per SIMD per cycle, recorded
